@@ -445,7 +445,11 @@ int chain_format(const dion2_options& opt, int ns_steps, ChainFmt* f) {
 
 double sym_flops(double s, double inner) { return s * (s + 1.0) * inner; }
 
-GemmArgs gram_args(const Plan& P, const uint16_t* Z, uint16_t* hi, uint16_t* lo) {
+// `scratch` (the O buffer, free until the final product) takes the partial
+// sums of a Gram product whose long inner side is split over more blocks.
+// s_real: the side the s x s matrices are needed to, 0 for all of s_pad (a
+// chain shared by groups reads further than a narrower member's own side).
+GemmArgs gram_args(const Plan& P, const uint16_t* Z, uint16_t* hi, uint16_t* lo, float* scratch, int64_t s_real) {
     GemmArgs g{};
     g.batch = P.batch;
     g.A0 = g.B0 = Z;
@@ -457,6 +461,9 @@ GemmArgs gram_args(const Plan& P, const uint16_t* Z, uint16_t* hi, uint16_t* lo)
     g.out1 = lo;
     g.sOut0 = g.sOut1 = P.s_pad * P.s_pad;
     g.ldo0 = g.ldo1 = (int)P.s_pad;
+    g.mreal = (int)round_up(s_real, 64);
+    g.part = scratch;
+    g.part_floats = (int64_t)P.batch * P.s_pad * P.l_pad;
     return g;
 }
 
@@ -478,6 +485,7 @@ GemmArgs sym3_args(const Plan& P, const uint16_t* xh, const uint16_t* xl, const 
     q.out1 = ol;
     q.sOut0 = q.sOut1 = P.s_pad * P.s_pad;
     q.ldo0 = q.ldo1 = (int)P.s_pad;
+    q.mreal = (int)round_up(P.s_k, 64);
     return q;
 }
 
@@ -556,10 +564,11 @@ hipError_t ns_direct(const Plan& P, uint16_t* Z0, uint16_t* Z1, uint16_t* const*
     for (int t = 0; t < ns_steps; ++t) {
         const float* cf = opt.ns_coeffs ? opt.ns_coeffs + 3 * t : kMuonQuintic;
         uint16_t* Z = zbuf[cur];
-        GemmArgs g = gram_args(P, Z, sq[SQ_AHI], a16 ? nullptr : sq[SQ_ALO]);
+        GemmArgs g = gram_args(P, Z, sq[SQ_AHI], a16 ? nullptr : sq[SQ_ALO], O, P.s_k);
         if (a16) g.oexp = eA;
-        hipError_t e = timed(DION2_PHASE_NS_GRAM, sym_flops(s_r, l_r) * nb, gram_bytes, 1, stream,
-                             [&] { return launch_gemm(g, a16 ? EPI_H16 : EPI_SPLIT, 1, stream); });
+        const GemmEpi ge = a16 ? EPI_H16 : EPI_SPLIT;
+        hipError_t e = timed(DION2_PHASE_NS_GRAM, sym_flops(s_r, l_r) * nb, gram_bytes, gemm_launches(g, ge, 1), stream,
+                             [&] { return launch_gemm(g, ge, 1, stream); });
         if (e != hipSuccess) return e;
 
         GemmArgs q = sym3_args(P, sq[SQ_AHI], sq[SQ_ALO], sq[SQ_AHI], sq[SQ_ALO], sq[SQ_B], nullptr);
@@ -625,19 +634,20 @@ hipError_t ns_direct(const Plan& P, uint16_t* Z0, uint16_t* Z1, uint16_t* const*
 
 // A_0 = Z Z^T as a hi / lo pair, or in fp16 (scaled) for the fp16 chain.
 // With Zlo (the fp32 master) Z is the pair Z + Zlo: three passes.
-hipError_t gram_a0(const Plan& P, const uint16_t* Z, const uint16_t* Zlo, uint16_t* Ah, uint16_t* Al,
-                   const ChainFmt& fmt, hipStream_t stream) {
+hipError_t gram_a0(const Plan& P, const uint16_t* Z, const uint16_t* Zlo, uint16_t* Ah, uint16_t* Al, float* O,
+                   int64_t s_real, const ChainFmt& fmt, hipStream_t stream) {
     const double s_r = (double)(P.k < P.d_oth ? P.k : P.d_oth);
     const double l_r = (double)(P.k < P.d_oth ? P.d_oth : P.k);
     const double nb = (double)P.batch;
     const int npass = Zlo ? 3 : 1;
     // Z in (hi, and lo), A out (hi + lo, or fp16)
     const double gram_bytes = ((Zlo ? 4.0 : 2.0) * s_r * l_r + (fmt.f16 ? 2.0 : 4.0) * s_r * s_r) * nb;
-    GemmArgs g = gram_args(P, Z, Ah, fmt.f16 ? nullptr : Al);
+    GemmArgs g = gram_args(P, Z, Ah, fmt.f16 ? nullptr : Al, O, s_real);
     if (fmt.f16) g.oexp = fmt.eA;
     if (Zlo) g.A1 = g.B1 = Zlo;
-    return timed(DION2_PHASE_NS_GRAM, npass * sym_flops(s_r, l_r) * nb, gram_bytes, 1, stream,
-                 [&] { return launch_gemm(g, fmt.f16 ? EPI_H16 : EPI_SPLIT, npass, stream); });
+    const GemmEpi epi = fmt.f16 ? EPI_H16 : EPI_SPLIT;
+    return timed(DION2_PHASE_NS_GRAM, npass * sym_flops(s_r, l_r) * nb, gram_bytes, gemm_launches(g, epi, npass), stream,
+                 [&] { return launch_gemm(g, epi, npass, stream); });
 }
 
 // Work of one group's s x s products, for the profiler. Per step: Q_t (from
@@ -859,7 +869,7 @@ hipError_t ns_gram(const Plan& P, const uint16_t* Z, const uint16_t* Zlo, uint16
                    hipStream_t stream) {
     const bool fused = fused_chain(P.s_k, opt);
     const ChainFmt cf = chain_fmt_for(fmt, f16_chain(fmt, fused, P));
-    hipError_t e = gram_a0(P, Z, Zlo, sq[SQ_AHI], sq[SQ_ALO], cf, stream);
+    hipError_t e = gram_a0(P, Z, Zlo, sq[SQ_AHI], sq[SQ_ALO], O, P.s_k, cf, stream);
     if (e != hipSuccess) return e;
     int cur = 0;
     e = gram_chain(P.batch, P.s_pad, P.s_k, sq, ns_steps, opt, cf, chain_cost(P, ns_steps, cf, fused), stream,
@@ -1519,8 +1529,8 @@ int groups_impl(const dion2_group* groups, int ngroups, float alpha, float mu, f
         if (st != DION2_OK) return st;
         fins[g] = make_final(P, ms, b, lr, ns_steps, gopt[g]);
         if (c >= 0) {
-            e = gram_a0(P, b.Z0, P.master ? b.Z1 : nullptr, b.sbuf[SQ_AHI], b.sbuf[SQ_ALO],
-                        chain_fmt_for(fmt, chains[c].f16), s);
+            e = gram_a0(P, b.Z0, P.master ? b.Z1 : nullptr, b.sbuf[SQ_AHI], b.sbuf[SQ_ALO], b.O,
+                        0, chain_fmt_for(fmt, chains[c].f16), s);
             if (e != hipSuccess) return hip_fail(e, "launch K4 Gram");
             if (nS > 1) {
                 e = hipEventRecord(ev_a0[g], s);

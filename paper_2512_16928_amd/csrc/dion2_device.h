@@ -283,8 +283,10 @@ hipError_t launch_copy_compact(const CompactCopyArgs& a, hipStream_t s);
 // The symmetric products (EPI_SPLIT, EPI_POLY, EPI_QPOLY, EPI_H16,
 // EPI_QPOLY_H16, EPI_POLY_H16) compute the tiles on and above the diagonal
 // and mirror them.
+//   EPI_PART   a symmetric product's partial sums over one part of K, left in
+//              `part` for a second launch (internal to launch_gemm)
 enum GemmEpi { EPI_SPLIT = 0, EPI_POLY = 1, EPI_UPDATE = 2, EPI_FINAL = 3, EPI_QPOLY = 4,
-               EPI_APPLY = 5, EPI_H16 = 6, EPI_QPOLY_H16 = 7, EPI_POLY_H16 = 8 };
+               EPI_APPLY = 5, EPI_H16 = 6, EPI_QPOLY_H16 = 7, EPI_POLY_H16 = 8, EPI_PART = 9 };
 struct GemmArgs {
     const uint16_t* A0; const uint16_t* A1;   // A operand(s), [M][K] ld lda
     const uint16_t* B0; const uint16_t* B1;   // B operand(s), [N][K] or [K][N], ld ldb
@@ -310,6 +312,15 @@ struct GemmArgs {
     // fp16 Gram-form chain: fp16 operands, and the scale exponents above
     int f16;
     int oexp, oexpx, eexp, sexp;
+    // symmetric products: the side their output is needed to (a multiple of
+    // 64; 0: all of M). Tiles past it may be left unwritten: nothing in them
+    // reaches a real entry, since every sum over s stops there.
+    int mreal;
+    // symmetric products whose K launch_gemm may split: scratch of part_floats
+    // fp32 values for the partial sums (null: never split), and the parts
+    float* part;
+    int64_t part_floats;
+    int ksplit;
     // EPI_APPLY only
     MatSet ms;                                 // W
     const int32_t* sel;                        // [batch][k]
@@ -319,6 +330,8 @@ struct GemmArgs {
     float* dbg;                                // nullable [batch][k][d_oth]
 };
 hipError_t launch_gemm(const GemmArgs& a, GemmEpi epi, int npass, hipStream_t s);
+// How many kernels that call launches: two where K is split.
+int gemm_launches(const GemmArgs& a, GemmEpi epi, int npass);
 
 // The GRAM form's chain of s x s products for s <= 64 (s_k, the K extent,
 // 32 or 64) in one launch, one block per matrix: A_0 in, P_T out, both as

@@ -49,6 +49,7 @@
 //
 // All dimensions are multiples of the tile (compact buffers are zero padded
 // to 128, and the padding stays zero through every step).
+#include <algorithm>
 #include <type_traits>
 
 #include "dion2_device.h"
@@ -361,6 +362,11 @@ __global__ __launch_bounds__(T::THREADS) void gemm(GemmArgs a) {
     const int hw = blockIdx.x + nx * (blockIdx.y + ny * blockIdx.z);
     const int logical = (total % kXcds == 0) ? (hw % kXcds) * (total / kXcds) + hw / kXcds : hw;
     int b = logical / (nx * ny);
+    int part = 0;
+    if constexpr (EPI == EPI_PART) {   // z runs over (matrix, part of K)
+        part = b % a.ksplit;
+        b /= a.ksplit;
+    }
     if (a.dual) {
         // matrix b's two products are neighbours in the tile order, so the
         // shared A operand is fetched into one L2 for both
@@ -468,7 +474,17 @@ __global__ __launch_bounds__(T::THREADS) void gemm(GemmArgs a) {
     // iteration kt slice kt+S-1 is requested into the stage freed by kt-1.
     // Requests past the last slice re-read it (in bounds) so every iteration
     // issues the same number of loads and the vmcnt wait stays exact.
-    const int nk = a.K / T::BK;
+    int nk = a.K / T::BK;
+    if constexpr (EPI == EPI_PART) {
+        // this part's slices: the parts' lengths differ by at most one slice
+        const int k0 = nk * part / a.ksplit;
+        nk = nk * (part + 1) / a.ksplit - k0;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            abase[h] += (int64_t)k0 * T::BK;
+            bbase[h] += (int64_t)k0 * T::BK;
+        }
+    }
 #pragma unroll
     for (int p = 0; p < T::S - 1; ++p)
         load_slice<NPASS, T>(a, smem_raw + p * T::STAGE_BYTES, p < nk ? p : nk - 1, abase, bbase, wave, lane);
@@ -485,6 +501,25 @@ __global__ __launch_bounds__(T::THREADS) void gemm(GemmArgs a) {
     }
     wait_vmcnt<0>();   // no load may land in the ring once the epilogue reuses it
     __syncthreads();
+
+    if constexpr (EPI == EPI_PART) {
+        // the accumulators as they are, in register order (16 bytes a lane,
+        // 1 KB an instruction); reduce_parts reads them back the same way
+        const int tiles = nx;
+        const int tile = logical % nx;
+        float* out = a.part + (((int64_t)b * a.ksplit + part) * tiles + tile) * (T::BM * T::BN);
+#pragma unroll
+        for (int i = 0; i < T::FM; ++i)
+#pragma unroll
+            for (int j = 0; j < T::FN; ++j) {
+                const int blk = (wm * T::FM + i) * (T::BN / 32) + wn * T::FN + j;
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    stg(out + blk * 1024 + q * 256 + lane * 4,
+                        make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]));
+            }
+        return;
+    }
 
     // ---- epilogue, one 32 x 32 block at a time through a per-wave LDS tile.
     // The tile belongs to its wave alone and LDS accesses of one wave complete
@@ -653,6 +688,80 @@ __global__ __launch_bounds__(T::THREADS) void gemm(GemmArgs a) {
     }
 }
 
+// C = the sum over the parts of K, in their order, of a product computed by
+// EPI_PART launches, in EPI's output form and exactly symmetric, as gemm's
+// own epilogue stores it. A wave takes one 32 x 32 block of a tile; blocks
+// below the diagonal are the mirrors of others. Bound by latency: a launch
+// of few tiles has a few MB of partials, which its own loads fetch at once.
+template <int EPI, typename T>
+__global__ __launch_bounds__(256) void reduce_parts(GemmArgs a) {
+    __shared__ float smem[4 * 32 * T::EPI_LD];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    constexpr int PER = (T::BM / 32) * (T::BN / 32);   // blocks of a tile
+    static_assert(PER % 4 == 0, "a block of four waves stays inside one tile");
+    const int tiles = a.M / T::BM;
+    const int ntile = tiles * (tiles + 1) / 2;
+    const int64_t w = (int64_t)blockIdx.x * 4 + wave;
+    const int blk = (int)(w % PER);
+    const int tile = (int)(w / PER % ntile);
+    const int b = (int)(w / PER / ntile);
+    int rem = tile, I = 0;
+    while (rem >= tiles - I) {
+        rem -= tiles - I;
+        ++I;
+    }
+    const int R = I * T::BM + 32 * (blk / (T::BN / 32));
+    const int C = (I + rem) * T::BN + 32 * (blk % (T::BN / 32));
+    if (R > C) return;   // whole wave; no block barrier follows
+    const float* in = a.part + ((int64_t)b * a.ksplit * ntile + tile) * (T::BM * T::BN) + blk * 1024 + lane * 4;
+    const int64_t step = (int64_t)ntile * (T::BM * T::BN);
+    float v[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) v[q] = 0.f;
+    int p = 0;
+    for (; p + 4 <= a.ksplit; p += 4) {   // sixteen loads in flight
+        float4 x[4][4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) x[u][q] = ldg<float4>(in + (p + u) * step + q * 256);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                v[4 * q] += x[u][q].x;
+                v[4 * q + 1] += x[u][q].y;
+                v[4 * q + 2] += x[u][q].z;
+                v[4 * q + 3] += x[u][q].w;
+            }
+    }
+    for (; p < a.ksplit; ++p) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float4 x = ldg<float4>(in + p * step + q * 256);
+            v[4 * q] += x.x;
+            v[4 * q + 1] += x.y;
+            v[4 * q + 2] += x.z;
+            v[4 * q + 3] += x.w;
+        }
+    }
+    const float osc = EPI == EPI_H16 ? __builtin_amdgcn_ldexpf(1.0f, a.oexp) : 1.0f;
+    float* stage = smem + wave * 32 * T::EPI_LD;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int m = (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
+        stage[m * T::EPI_LD + (lane & 31)] = EPI == EPI_H16 ? v[r] * osc : v[r];
+    }
+    __builtin_amdgcn_wave_barrier();   // LDS accesses of one wave complete in issue order
+    if (R == C) {
+        store_block<EPI, T, false, true>(a, b, stage, (int64_t)R, (int64_t)C, lane);
+    } else {
+        store_block<EPI, T, false>(a, b, stage, (int64_t)R, (int64_t)C, lane);
+        store_block<EPI, T, true>(a, b, stage, (int64_t)C, (int64_t)R, lane);
+    }
+}
+
 // ---- the GRAM chain of a compact matrix with s <= 64, in one block
 //
 // The s x s matrices stay in LDS as bf16 hi / lo planes of 64 rows (pitch
@@ -803,8 +912,8 @@ constexpr unsigned kMaxGridZ = 65535;   // the grid's z extent holds the batch
 template <int NPASS, int EPI, typename T, bool SYM = false>
 hipError_t launch_tile(const GemmArgs& a, hipStream_t s) {
     if (a.M % T::BM || a.N % T::BN || a.K % T::BK) return hipErrorInvalidValue;
-    const unsigned per = a.dual ? 2u : 1u;
-    if (SYM && (unsigned)a.batch * per > kMaxGridZ) {
+    const unsigned per = EPI == EPI_PART ? (unsigned)a.ksplit : a.dual ? 2u : 1u;
+    if (SYM && EPI != EPI_PART && (unsigned)a.batch * per > kMaxGridZ) {
         // A dual launch of more than 32767 matrices: consecutive launches
         // over slices of the batch (the symmetric products' operands and
         // outputs are all bf16 / fp16 stacks with a batch stride).
@@ -844,16 +953,204 @@ hipError_t launch_tile(const GemmArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
+// A symmetric product in two launches: the parts of K, then their sum.
+template <int NPASS, int EPI, typename T>
+hipError_t launch_split(const GemmArgs& a, hipStream_t s) {
+    const hipError_t e = launch_tile<NPASS, EPI_PART, T, true>(a, s);
+    if (e != hipSuccess) return e;
+    const int64_t tiles = a.M / T::BM;
+    const int64_t waves = (int64_t)a.batch * (tiles * (tiles + 1) / 2) * (T::BM / 32) * (T::BN / 32);
+    hipLaunchKernelGGL((reduce_parts<EPI, T>), dim3((unsigned)(waves / 4)), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
+// ---- tile and split choices
+//
+// 256 compute units take two blocks of any of these tiles at once (one of a
+// 256 x 256 tile), so a launch of few tiles leaves most of the chip idle and
+// costs one block's serial time: the slice loop's latency and a big tile's
+// epilogue. There the tile shrinks to 64 x 64 (four times the blocks, each
+// with four slices in flight), and a long K is split over more blocks, whose
+// fp32 partials a second launch folds in order. A larger launch is bound by
+// the path into LDS, where a small tile's lower reuse costs more than the
+// fuller chip gains. Every choice computes each entry's sum in one order (per
+// 16-deep k-step hi lo, lo hi, hi hi), so they are bitwise alike except where
+// K is split, which only a symmetric product over the long side does.
+// Measured (us per launch, 128 x 128 tiles before, chosen tile after):
+//   three-pass s x s products: s = 256, batch 1: 8.7, 4.6; s = 512, batch 1:
+//     13.2, 6.0 and batch 16: 17.9, 16.7; s = 1024, batch 1: 27.9, 10.7
+//   Gram matrix, s x l: 256 x 1024: 11.6, 6.4; 512 x 2048, batch 4: 19.0,
+//     10.3; 512 x 8192: 58.7, 13.0; 256 x 8192, batch 8: 58.5, 16.3; 1024 x
+//     4096, batch 4: 90.0 on 256 x 256 tiles, 35.8
+//   two-pass final product, s x l: 256 x 1024: 7.7, 5.9; 1024 x 4096: 29.3, 22.8
+enum SymTile { SYM_64, SYM_64S2, SYM_128, SYM_256 };
+struct SymPlan {
+    SymTile tile;
+    int ksplit;
+};
+
+int64_t sym_tiles(const GemmArgs& a, int m, int bm) {
+    const int64_t t = (m + bm - 1) / bm;
+    return (int64_t)a.batch * (a.dual ? 2 : 1) * (t * (t + 1) / 2);
+}
+
+// Parts of K for a launch of n tiles: as many as `most` blocks hold, none of
+// them shorter than `least`, and no more than the scratch holds.
+int parts_of(const GemmArgs& a, int64_t n, int bm, int m, int64_t most, int least) {
+    const int64_t t = (m + bm - 1) / bm;
+    const int64_t floats = (int64_t)a.batch * (t * (t + 1) / 2) * bm * bm;
+    int64_t p = std::min(most / n, (int64_t)(a.K / least));
+    if (floats * p > a.part_floats) p = a.part_floats / floats;
+    return p < 2 ? 1 : (int)p;
+}
+
+SymPlan plan_sym(const GemmArgs& a, GemmEpi epi, int npass) {
+    const bool split = a.part && !a.dual && !a.f16 && (epi == EPI_SPLIT || epi == EPI_H16);
+    const int mr = a.mreal ? a.mreal : a.M;   // 64 x 64 tiles stop at the real side
+    const int64_t n64 = sym_tiles(a, mr, 64), n128 = sym_tiles(a, a.M, 128);
+    const int64_t n256 = a.M % 256 ? 0 : sym_tiles(a, a.M, 256);
+    if (npass == 3) {
+        // one block a compute unit: four stages; up to about 700 blocks
+        // three of the two-stage ring's share one (544 at s = 1024: 26.8
+        // against 30.4 us; 1152 at s = 512: 29.8 against 28.2)
+        if (n64 <= 256) return {SYM_64, split && a.K >= 1024 ? parts_of(a, n64, 64, mr, 256, 512) : 1};
+        if (n64 <= 704) return {SYM_64S2, 1};
+        // two rounds of 256 x 256 tiles for the plain products (the
+        // polynomial epilogues spill on them): 5-10% at s = 1024 and 2048
+        const bool poly = epi == EPI_POLY || epi == EPI_QPOLY;
+        return {!poly && a.M >= 1024 && n256 >= 512 ? SYM_256 : SYM_128, 1};
+    }
+    if (n64 <= 256) {
+        // below K = 2048 the second launch costs more than the shorter loop
+        // saves (1024 deep: 6.4 against 7.5 us); from 4096 on two blocks a
+        // compute unit pay (1024 x 4096: 15.6 us in three parts, 18.0 whole)
+        const int64_t most = a.K >= 4096 && n64 > 128 ? 512 : 256;
+        return {SYM_64, split && a.K >= 2048 ? parts_of(a, n64, 64, mr, most, 640) : 1};
+    }
+    // 288 to 336 tiles of 64 x 64 measured 13.6 us at K = 2048 where 128 x 128
+    // took 19.5, 22.6 against 32.8 at 4096; 528 of them 23.9 against 20.7
+    if (n64 <= 448 && a.K < 8192) return {SYM_64, 1};
+    if (a.f16) return {a.M >= 2048 && n256 > 0 ? SYM_256 : SYM_128, 1};
+    // 256 x 256 tiles run one to a compute unit: they pay once their last
+    // round is filled well (s = 2048: 144 tiles 57.8 against 62.0 us, 288
+    // tiles 116.6 against 104.6; s = 1024, 160 tiles: 201 against 215)
+    const int64_t rounds = (n256 + 255) / 256;
+    if (a.M >= 1024 && n256 >= (rounds == 1 ? 140 : 160 * rounds)) return {SYM_256, 1};
+    return {SYM_128, split && a.K >= 4096 ? parts_of(a, n128, 128, a.M, 256, 1024) : 1};
+}
+
+bool is_sym(GemmEpi epi) { return epi != EPI_UPDATE && epi != EPI_FINAL && epi != EPI_APPLY; }
+
+// A symmetric product on tile T, whole or split over K.
+template <int NPASS, int EPI, typename T>
+hipError_t launch_sym(const GemmArgs& a0, int ksplit, hipStream_t s) {
+    GemmArgs a = a0;
+    if (T::BM == 64 && a.mreal) a.M = a.N = a.mreal;
+    a.K = (a.K + T::BK - 1) / T::BK * T::BK;   // operands are zero to the next 128
+    a.ksplit = ksplit;
+    if constexpr ((EPI == EPI_SPLIT || EPI == EPI_H16) && !T::F16) {
+        if (ksplit > 1) return launch_split<NPASS, EPI, T>(a, s);
+    }
+    return ksplit > 1 ? hipErrorInvalidValue : launch_tile<NPASS, EPI, T, true>(a, s);
+}
+
+// The tiles: 128 x 128 with four stages of 32-deep slices (two blocks of four
+// waves per CU) for one-pass products, 256 x 256 for large ones; three-pass
+// products 128 x 128 in a two-stage ring of eight waves. The fp16 s x s
+// products run on 256 x 256 from s = 2048 (12% faster there, 24% at 4096; 13%
+// slower at 1024).
+template <int EPI>
+hipError_t sym_one(const GemmArgs& a, const SymPlan& p, hipStream_t s) {
+    switch (p.tile) {
+        case SYM_64: return launch_sym<1, EPI, Tile<1, 0, 64, 64, 64, 2, 2, 4>>(a, p.ksplit, s);
+        case SYM_256: return launch_sym<1, EPI, Tile<1, 0, 256, 256, kSliceK, 4, 2, 3>>(a, 1, s);
+        default: return launch_sym<1, EPI, Tile<1, 0, 128, 128, kSliceK, 2, 2, 4>>(a, p.ksplit, s);
+    }
+}
+template <int EPI>
+hipError_t sym_f16(const GemmArgs& a, const SymPlan& p, hipStream_t s) {
+    switch (p.tile) {
+        case SYM_64: return launch_sym<1, EPI, Tile<1, 0, 64, 64, 64, 2, 2, 4, true>>(a, 1, s);
+        case SYM_256: return launch_sym<1, EPI, Tile<1, 0, 256, 256, kSliceK, 4, 2, 3, true>>(a, 1, s);
+        default: return launch_sym<1, EPI, Tile<1, 0, 128, 128, kSliceK, 2, 2, 4, true>>(a, 1, s);
+    }
+}
+template <int EPI>
+hipError_t sym_three(const GemmArgs& a, const SymPlan& p, hipStream_t s) {
+    switch (p.tile) {
+        case SYM_64: return launch_sym<3, EPI, Tile<3, 0, 64, 64, kSliceK, 2, 2, 4>>(a, p.ksplit, s);
+        case SYM_64S2: return launch_sym<3, EPI, Tile<3, 0, 64, 64, kSliceK, 2, 2, 2>>(a, 1, s);
+        case SYM_256:
+            if constexpr (EPI == EPI_SPLIT) return launch_sym<3, EPI, Tile<3, 0, 256, 256, kSliceK, 2, 4, 2>>(a, 1, s);
+            return hipErrorInvalidValue;
+        default: return launch_sym<3, EPI, Tile<3, 0, 128, 128, kSliceK, 4, 2, 2>>(a, 1, s);
+    }
+}
+
+hipError_t launch_sym_product(const GemmArgs& a, GemmEpi epi, int npass, hipStream_t s) {
+    const SymPlan p = plan_sym(a, epi, npass);
+    if (a.f16) {
+        if (npass != 1 || (a.dual && epi != EPI_H16)) return hipErrorInvalidValue;   // dual: the chain's P and T
+        switch (epi) {
+            case EPI_SPLIT: return sym_f16<EPI_SPLIT>(a, p, s);
+            case EPI_H16: return sym_f16<EPI_H16>(a, p, s);
+            case EPI_QPOLY_H16: return sym_f16<EPI_QPOLY_H16>(a, p, s);
+            case EPI_POLY_H16: return sym_f16<EPI_POLY_H16>(a, p, s);   // the Direct form's B = b A + c A^2
+            default: return hipErrorInvalidValue;
+        }
+    }
+    if (a.dual && !(epi == EPI_SPLIT && npass == 3)) return hipErrorInvalidValue;
+    if (npass == 1) {   // the Gram matrix (EPI_H16: into the fp16 chain or the Direct form)
+        if (epi == EPI_SPLIT) return sym_one<EPI_SPLIT>(a, p, s);
+        if (epi == EPI_H16) return sym_one<EPI_H16>(a, p, s);
+    } else if (npass == 3) {
+        if (epi == EPI_SPLIT) return sym_three<EPI_SPLIT>(a, p, s);
+        if (epi == EPI_POLY) return sym_three<EPI_POLY>(a, p, s);
+        if (epi == EPI_QPOLY) return sym_three<EPI_QPOLY>(a, p, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+// X-side products with the [K][N] operand. A two-stage ring of 128 x 128
+// tiles leaves room for three blocks per CU; with the update applied in the
+// epilogue eight waves per block hide more of the W traffic. A launch of at
+// most one such tile a CU takes 64 x 128 tiles of eight waves in a deeper ring.
+template <int NPASS, int EPI>
+hipError_t launch_right(const GemmArgs& a, hipStream_t s) {
+    const int64_t n128 = (int64_t)a.batch * (a.M / 128) * (a.N / 128);
+    // (three passes: 256 tiles 21.6 us on 64 x 128, 20.7 on 128 x 128; 16
+    // tiles 6.8 against 11.1)
+    if (n128 <= (NPASS == 3 ? 128 : 256)) {
+        using T = Tile<NPASS, 1, 64, 128, NPASS == 1 ? 64 : kSliceK, 2, 4, NPASS == 1 ? 3 : 4>;
+        GemmArgs r = a;
+        r.K = (a.K + T::BK - 1) / T::BK * T::BK;   // operands are zero to the next 64
+        return launch_tile<NPASS, EPI, T>(r, s);
+    }
+    if constexpr (NPASS == 2 && EPI == EPI_APPLY)
+        return launch_tile<NPASS, EPI, Tile<2, 1, 128, 128, kSliceK, 4, 2, 2>>(a, s);
+    else
+        return launch_tile<NPASS, EPI, Tile<NPASS, 1, 128, 128, kSliceK, 2, 2, 2>>(a, s);
+}
+
+// The Direct form's X-side products from s = 2048: X^T as rows lets them run
+// on the wide plain-read tiles (28% faster at s = 2048, 35% at 4096 than the
+// transposing reads of the [K][N] operand): 256 x 256, or 256 x 128 where l
+// is not a multiple of 256 and for the fused update step (whose W rows spill
+// on 256 x 256).
+template <int EPI>
+hipError_t launch_rows(const GemmArgs& a, hipStream_t s) {
+    using TR = Tile<1, 0, 256, 256, kSliceK, 2, 4, 3>;
+    using TRN = Tile<1, 0, 256, 128, kSliceK, 4, 2, 4>;
+    if constexpr (EPI != EPI_APPLY) {
+        if (a.N % 256 == 0) return launch_tile<1, EPI, TR>(a, s);
+    }
+    return launch_tile<1, EPI, TRN>(a, s);
+}
+
 }  // namespace
 
-// A three-pass symmetric s x s product without a polynomial epilogue goes
-// on 256 x 256 tiles (one block of eight waves per compute unit) when s is
-// a multiple of 256 and the launch has enough of those tiles to fill the
-// chip twice; otherwise on 128 x 128.
-bool big_sym(const GemmArgs& a) {
-    if (a.M < 1024 || a.M % 256) return false;
-    const int64_t t = a.M / 256;
-    return (int64_t)a.batch * (a.dual ? 2 : 1) * (t * (t + 1) / 2) >= 512;
+int gemm_launches(const GemmArgs& a, GemmEpi epi, int npass) {
+    return is_sym(epi) && plan_sym(a, epi, npass).ksplit > 1 ? 2 : 1;
 }
 
 // bf16 transpose through a 64 x 64 LDS tile (row pitch 66 elements, so the
@@ -886,107 +1183,23 @@ __global__ __launch_bounds__(256) void transpose_bf16(const uint16_t* __restrict
 }
 
 hipError_t launch_gemm(const GemmArgs& a, GemmEpi epi, int npass, hipStream_t s) {
-    // Tile choices measured on MI355X at the Newton-Schulz shapes. The Gram
-    // matrix keeps four stages of 32-deep slices on 128 x 128 tiles, two
-    // blocks of four waves per CU (64-deep slices fetch whole 128-byte lines
-    // per row, but either cost blocks per CU, which slows the step whose
-    // groups run side by side, or a stage in flight); from s = 1024 it runs
-    // on 256 x 256 tiles.
-    // The fp16 s x s products (one pass) run on 128 x 128 tiles of four
-    // waves, and from s = 2048 on 256 x 256 tiles of eight (12% faster at
-    // s = 2048, 24% at 4096; 13% slower at 1024).
-    // The three-pass s x s products keep 128 x 128 tiles, two blocks per CU,
-    // except large launches of the plain (hi / lo) products, which run on
-    // 256 x 256. The X-side products use a two-stage ring, which leaves
-    // room for three blocks per CU; with the update applied in the
-    // epilogue eight waves per block hide more of the W traffic. Given X^T
-    // as rows (b_rows) they run on 256 x 256 plain-read tiles, or 256 x 128
-    // where l is not a multiple of 256 and for the fused update step.
-    using TG = Tile<1, 0, 128, 128, kSliceK, 2, 2, 4>;    // Gram
-    using TGL = Tile<1, 0, 256, 256, kSliceK, 4, 2, 3>;   // Gram, large s
-    using TP = Tile<3, 0, 128, 128, kSliceK, 4, 2, 2>;    // three-pass symmetric products
-    using TPL = Tile<3, 0, 256, 256, kSliceK, 2, 4, 2>;   // three-pass symmetric products, large s
-    using TU = Tile<1, 1, 128, 128, kSliceK, 2, 2, 2>;    // update (B operand [K][N])
-    using TU2 = Tile<2, 1, 128, 128, kSliceK, 2, 2, 2>;   // two-pass final product
-    using TU2A = Tile<2, 1, 128, 128, kSliceK, 4, 2, 2>;  // two-pass final product applying the update
-    using TU3 = Tile<3, 1, 128, 128, kSliceK, 2, 2, 2>;   // three-pass final product (fp32 master)
-    using TR = Tile<1, 0, 256, 256, kSliceK, 2, 4, 3>;    // X-side products, B operand as rows (X^T)
-    using TRN = Tile<1, 0, 256, 128, kSliceK, 4, 2, 4>;   // the same, l not a multiple of 256; fused update
-    using TH = Tile<1, 0, 128, 128, kSliceK, 2, 2, 4, true>;   // fp16 s x s products
-    using THL = Tile<1, 0, 256, 256, kSliceK, 4, 2, 3, true>;  // fp16 s x s products from s = 2048
-    if (a.f16) {
-        if (npass != 1) return hipErrorInvalidValue;
-        const bool big = a.M >= 2048 && a.M % 256 == 0;
-        if (a.dual && epi != EPI_H16) return hipErrorInvalidValue;   // the chain's P and T
-        switch (epi) {
-            case EPI_SPLIT:
-                return big ? launch_tile<1, EPI_SPLIT, THL, true>(a, s) : launch_tile<1, EPI_SPLIT, TH, true>(a, s);
-            case EPI_H16:
-                return big ? launch_tile<1, EPI_H16, THL, true>(a, s) : launch_tile<1, EPI_H16, TH, true>(a, s);
-            case EPI_QPOLY_H16:
-                return big ? launch_tile<1, EPI_QPOLY_H16, THL, true>(a, s)
-                           : launch_tile<1, EPI_QPOLY_H16, TH, true>(a, s);
-            case EPI_POLY_H16:   // the Direct form's B = b A + c A^2
-                return big ? launch_tile<1, EPI_POLY_H16, THL, true>(a, s)
-                           : launch_tile<1, EPI_POLY_H16, TH, true>(a, s);
-            default: break;
-        }
-        return hipErrorInvalidValue;
-    }
-    if (a.dual && !(epi == EPI_SPLIT && npass == 3)) return hipErrorInvalidValue;
+    if (is_sym(epi)) return launch_sym_product(a, epi, npass, s);
+    if (a.f16 || a.dual) return hipErrorInvalidValue;
+    if (epi == EPI_APPLY && (a.cols % 8 || a.cols < 16 || a.out_transposed)) return hipErrorInvalidValue;
     if (a.b_rows) {
-        // the Direct form's X-side products from s = 2048: X^T as rows lets
-        // them run on the wide plain-read tiles (28% faster at s = 2048, 35%
-        // at 4096 than the transposing reads of the [K][N] operand)
         if (npass != 1 || a.M % 256) return hipErrorInvalidValue;
-        const bool wide = a.N % 256 == 0;
-        switch (epi) {
-            case EPI_UPDATE:
-                return wide ? launch_tile<1, EPI_UPDATE, TR>(a, s) : launch_tile<1, EPI_UPDATE, TRN>(a, s);
-            case EPI_FINAL:
-                return wide ? launch_tile<1, EPI_FINAL, TR>(a, s) : launch_tile<1, EPI_FINAL, TRN>(a, s);
-            case EPI_APPLY:   // (its W rows spill on 256 x 256)
-                if (a.cols % 8 || a.cols < 16 || a.out_transposed) break;
-                return launch_tile<1, EPI_APPLY, TRN>(a, s);
-            default: break;
-        }
-        return hipErrorInvalidValue;
+        if (epi == EPI_UPDATE) return launch_rows<EPI_UPDATE>(a, s);
+        return epi == EPI_FINAL ? launch_rows<EPI_FINAL>(a, s) : launch_rows<EPI_APPLY>(a, s);
     }
-    switch (epi) {
-        case EPI_SPLIT:
-            if (npass == 3) {
-                if (big_sym(a)) return launch_tile<3, EPI_SPLIT, TPL, true>(a, s);
-                return launch_tile<3, EPI_SPLIT, TP, true>(a, s);
-            }
-            if (npass != 1) break;
-            if (a.M >= 1024 && a.M % 256 == 0) return launch_tile<1, EPI_SPLIT, TGL, true>(a, s);
-            return launch_tile<1, EPI_SPLIT, TG, true>(a, s);
-        case EPI_H16:   // the Gram matrix of bf16 Z into the fp16 chain
-            if (npass != 1) break;
-            if (a.M >= 1024 && a.M % 256 == 0) return launch_tile<1, EPI_H16, TGL, true>(a, s);
-            return launch_tile<1, EPI_H16, TG, true>(a, s);
-        case EPI_POLY:   // (the polynomial epilogues keep 128 x 128: on 256 x 256 they spill)
-            if (npass == 3) return launch_tile<3, EPI_POLY, TP, true>(a, s);
-            break;
-        case EPI_QPOLY:
-            if (npass == 3) return launch_tile<3, EPI_QPOLY, TP, true>(a, s);
-            break;
-        case EPI_UPDATE:
-            if (npass == 1) return launch_tile<1, EPI_UPDATE, TU>(a, s);
-            break;
-        case EPI_FINAL:
-            if (npass == 1) return launch_tile<1, EPI_FINAL, TU>(a, s);
-            if (npass == 2) return launch_tile<2, EPI_FINAL, TU2>(a, s);
-            if (npass == 3) return launch_tile<3, EPI_FINAL, TU3>(a, s);
-            break;
-        case EPI_APPLY:
-            if (a.cols % 8 || a.cols < 16 || a.out_transposed) break;
-            if (npass == 1) return launch_tile<1, EPI_APPLY, TU>(a, s);
-            if (npass == 2) return launch_tile<2, EPI_APPLY, TU2A>(a, s);
-            if (npass == 3) return launch_tile<3, EPI_APPLY, TU3>(a, s);
-            break;
-        default:   // the fp16 epilogues run only with fp16 operands (above)
-            break;
+    if (epi == EPI_UPDATE) return npass == 1 ? launch_right<1, EPI_UPDATE>(a, s) : hipErrorInvalidValue;
+    if (epi == EPI_FINAL) {
+        if (npass == 1) return launch_right<1, EPI_FINAL>(a, s);
+        if (npass == 2) return launch_right<2, EPI_FINAL>(a, s);
+        if (npass == 3) return launch_right<3, EPI_FINAL>(a, s);
+    } else if (epi == EPI_APPLY) {
+        if (npass == 1) return launch_right<1, EPI_APPLY>(a, s);
+        if (npass == 2) return launch_right<2, EPI_APPLY>(a, s);
+        if (npass == 3) return launch_right<3, EPI_APPLY>(a, s);
     }
     return hipErrorInvalidValue;
 }

@@ -1,0 +1,72 @@
+"""The Newton-Schulz products' tile and split choices, at the sizes where they change.
+
+A launch of few tiles runs on 64 x 64 tiles, a long K is split over blocks, and
+larger launches keep the bigger tiles. Without a split every choice computes
+each entry's sum in one order, so a matrix's step is bitwise the same whatever
+the batch it is in. With one it is checked against the oracle, within the
+bound every Newton-Schulz path has. The workspace starts as NaN bits: tiles
+past the compact matrix's real side are not written, and nothing in them may
+reach a real entry.
+"""
+import pytest
+import torch
+
+from paper_2512_16928_amd import binding, workloads
+from paper_2512_16928_amd.binding import AXIS_AUTO, CHAIN_F16, MASTER_FP32, NS_DIRECT, NS_GRAM, SELECT_RANDOM
+from test_gpu_parity import check_matrix, one_group_workload, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def nan_workspace(batch, rows, cols, alpha, device, **kw):
+    n = binding.dion2_workspace_size_ex(batch, rows, cols, alpha, AXIS_AUTO, 5, **kw)
+    return torch.full((n,), 0xFF, dtype=torch.uint8, device=device)
+
+
+@pytest.mark.parametrize("rows,cols,alpha,batches,kw", [
+    (260, 1030, 0.25, (1, 2, 90), {}),                           # s = 65: one 64-tile more than s fills
+    (1030, 516, 0.5, (1, 25, 26, 71), dict(ns_form=NS_GRAM)),    # s = 258, columns: 15 tiles, 375 and 390 blocks
+    (1000, 1000, 0.25, (1, 25, 26, 70, 71), dict(ns_form=NS_GRAM)),   # s = 250: 250, 260, 700 and 710 blocks
+    (640, 1000, 0.5, (1, 12, 17), dict(ns_form=NS_DIRECT)),      # s = 320: one-pass products at 252 and 357 blocks
+    (450, 700, 1.0, (1, 8, 13), {}),                             # s = 450, DIRECT, 448 sides written of 512
+    (960, 960, 0.25, (1, 26, 71), dict(ns_master=MASTER_FP32)),   # K = 960: the three-pass Gram splits from 1024
+    (516, 1030, 0.25, (1, 86), dict(ns_chain=CHAIN_F16)),        # s = 129, l = 8 s: fp16 products
+])
+def test_tiles_bitwise_across_batches(hip_device, rows, cols, alpha, batches, kw):
+    W, M, G = workloads.make_group(one_group_workload(rows, cols, name=f"tile{rows}x{cols}"), 0, hip_device)
+    first = None
+    for n in batches:
+        Wn, Mn, Gn = (t.repeat(n, 1, 1) for t in (W, M, G))
+        ws = nan_workspace(n, rows, cols, alpha, hip_device, **kw)
+        binding.dion2_step_ex(Wn, Mn, Gn, alpha, workspace=ws, **kw)
+        torch.cuda.synchronize()
+        got = Wn.view(torch.int16)
+        if first is None:
+            first = got[0].clone()
+        assert bool((got == first).all()), f"batch {n}"
+
+
+@pytest.mark.parametrize("rows,cols,alpha,batch,kw,tol", [
+    (260, 2050, 0.25, 1, {}, 2e-2),                              # K = 2080: three parts of unequal length
+    (2112, 260, 0.25, 7, {}, 2e-2),                              # columns
+    (128, 4100, 0.5, 2, {}, 2e-2),                               # s = 64: the one-launch chain after a split Gram
+    (516, 4200, 0.25, 2, dict(ns_master=MASTER_FP32), 2e-3),     # three passes
+    (640, 2100, 0.5, 1, dict(ns_form=NS_DIRECT), 2e-2),          # fp16 A from parts, every step
+    (520, 2176, 0.25, 1, dict(ns_chain=CHAIN_F16), 2e-2),        # into the fp16 chain
+    (2304, 392, 0.25, 1, dict(select_rule=SELECT_RANDOM), 2e-2),  # the unscaled columns left O before the parts came
+    (128, 8192, 1.0, 90, {}, 2e-2),                              # 128 x 128 tiles, two parts
+])
+def test_split_k(hip_device, rows, cols, alpha, batch, kw, tol):
+    W, M, G = workloads.make_group(one_group_workload(rows, cols, count=batch, name=f"split{rows}x{cols}"), 0, hip_device)
+    run = dict(form=kw.get("ns_form", binding.NS_AUTO), chain=kw.get("ns_chain", binding.CHAIN_HILO),
+               master=kw.get("ns_master", binding.MASTER_BF16))
+    if "select_rule" in kw:
+        run.update(rand=(0, 0, 0), norms=False)
+    W2, M2 = W.clone(), M.clone()
+    res = run_gpu(W, M, G, alpha, **run)
+    for b in (0, batch - 1):
+        check_matrix(res, b, alpha, ns_tol=tol, rand=run.get("rand"))
+    ws = nan_workspace(batch, rows, cols, alpha, hip_device, **kw)
+    binding.dion2_step_ex(W2, M2, G, alpha, workspace=ws, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(W2.cpu().view(torch.int16), res["W"].view(torch.int16)) and torch.equal(M2.cpu(), res["M"])
