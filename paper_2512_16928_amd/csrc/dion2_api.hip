@@ -157,10 +157,15 @@ int make_plan(int batch, int64_t rows, int64_t cols, float alpha, int axis, int 
     // read; the compact matrix is normalised once every row is in.
     P.colpass = random_rule && P.axis == 1 && !P.master && ns_steps > 0;
     P.batch = batch;
-    P.nrb = P.axis == 1 ? (int)momentum_col_blocks(rows, &P.rb_rows) : 0;
-    if (P.axis == 0) P.rb_rows = 0;
 
     const size_t B = (size_t)batch;
+    const size_t comp = B * (size_t)P.kpad * (size_t)P.opad * 2;
+    // The column norms' partial sums are consumed before the selection is
+    // known, so they share the memory of everything written after it; the
+    // compact matrix and O alone bound them (every plan of a shape has those,
+    // so its row blocks are the same in a grouped call).
+    P.rb_rows = 0;
+    P.nrb = P.axis == 1 ? (int)momentum_col_blocks(rows, cols, batch, 3 * comp, &P.rb_rows) : 0;
     size_t off = 0;
     auto take = [&](size_t bytes) {
         size_t o = off;
@@ -169,11 +174,10 @@ int make_plan(int batch, int64_t rows, int64_t cols, float alpha, int axis, int 
     };
     P.o_l1 = take(B * P.d_sel * 8);
     P.o_sq = take(B * P.d_sel * 8);
-    P.o_part = take(P.axis == 1 ? B * P.nrb * 3 * (size_t)cols * 8 : 0);
+    P.o_part = off;
     P.o_sel = take(B * P.k * 4);
     P.o_rank = take(P.axis == 1 ? B * (size_t)(P.d_sel + 1) * 4 : 0);
     P.o_scale = take(B * 8);
-    const size_t comp = B * (size_t)P.kpad * (size_t)P.opad * 2;
     P.o_Z = take(comp);
     P.o_Z1 = take(P.gram && !P.master ? 0 : comp);   // DIRECT's ping-pong copy, or the lo half of X
     P.o_ZT = take(P.xrows ? 2 * comp : 0);            // DIRECT's X^T, ping-pong
@@ -181,6 +185,8 @@ int make_plan(int batch, int64_t rows, int64_t cols, float alpha, int axis, int 
     P.S_bytes = align256(B * (size_t)P.s_pad * (size_t)P.s_pad * 2);
     P.o_S = take(own_sq ? P.S_bytes * (P.gram ? SQ_GRAM_COUNT : SQ_DIRECT_COUNT) : 0);
     P.o_O = take(B * (size_t)P.kpad * (size_t)P.opad * 4);
+    // (the norm pass already reads the pointer tables)
+    off = std::max(off, align256(P.o_part + (P.axis == 1 ? B * P.nrb * 3 * (size_t)cols * 8 : 0)));
     P.o_tables = take(3 * B * sizeof(void*));
     P.total = off;
     return DION2_OK;

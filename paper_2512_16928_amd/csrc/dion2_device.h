@@ -183,7 +183,8 @@ struct MomentumArgs {
     float mu;          // used when decay_all (M <- mu (M + G) after use)
 };
 hipError_t launch_momentum(const MomentumArgs& a, int axis, int g_bf16, hipStream_t s);
-int64_t momentum_col_blocks(int64_t rows, int* rb_rows);
+// row blocks and their height for partials of at most part_bytes (or of 256-row blocks)
+int64_t momentum_col_blocks(int64_t rows, int64_t cols, int batch, size_t part_bytes, int* rb_rows);
 
 struct SelectArgs {
     const double* l1;

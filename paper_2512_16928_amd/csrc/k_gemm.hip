@@ -1010,11 +1010,13 @@ SymPlan plan_sym(const GemmArgs& a, GemmEpi epi, int npass) {
     const int64_t n64 = sym_tiles(a, mr, 64), n128 = sym_tiles(a, a.M, 128);
     const int64_t n256 = a.M % 256 ? 0 : sym_tiles(a, a.M, 256);
     if (npass == 3) {
-        // one block a compute unit: four stages; up to about 700 blocks
+        // one block a compute unit: four stages; up to 560 blocks two or
         // three of the two-stage ring's share one (544 at s = 1024: 26.8
-        // against 30.4 us; 1152 at s = 512: 29.8 against 28.2)
+        // against 30.4 us; 1152 at s = 512: 29.8 against 28.2; 576 at s =
+        // 512 16.7 against 17.9 alone, but the grouped call of the 1B stack,
+        // whose other groups use the same caches, 0.6% slower)
         if (n64 <= 256) return {SYM_64, split && a.K >= 1024 ? parts_of(a, n64, 64, mr, 256, 512) : 1};
-        if (n64 <= 704) return {SYM_64S2, 1};
+        if (n64 <= 560) return {SYM_64S2, 1};
         // two rounds of 256 x 256 tiles for the plain products (the
         // polynomial epilogues spill on them): 5-10% at s = 1024 and 2048
         const bool poly = epi == EPI_POLY || epi == EPI_QPOLY;

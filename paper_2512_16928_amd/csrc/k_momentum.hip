@@ -111,60 +111,127 @@ __global__ __launch_bounds__(kThreads) void momentum_rows(MatSet ms, int64_t row
     }
 }
 
-template <int VEC, typename GT>
+// Column mode, partial sums of a block of rb_rows rows, kColUnroll rows of a
+// wave loaded at once. With WIDE a block of four waves covers 256 VEC adjacent
+// columns; without, 64 VEC, each wave a contiguous quarter of the rows, and
+// the quarters are folded in row order. Large launches whose rows the wide
+// blocks tile exactly keep them: 4 KB of a row together stream better (16 x
+// 8192 x 2048: 246 against 270 us; 64 x 2048 x 1408, which they do not tile,
+// 191 us on the narrow ones against 222 on single waves). Bound by memory once enough rows are in flight: the row blocks shrink with
+// the launch (momentum_col_blocks), since 256 rows a thread left one 8192 x
+// 2048 matrix 64 blocks and 145 us, where 64 rows a block take 24.
+constexpr int kColUnroll = 8;
+
+template <int VEC, typename GT, bool WIDE>
 __global__ __launch_bounds__(kThreads) void momentum_cols_partial(MatSet ms, int64_t rows,
                                                                   int64_t cols, int rb_rows,
                                                                   int nrb,
                                                                   double* __restrict__ part) {
+    constexpr int kW = WIDE ? 1 : kThreads / 64;   // waves that share a column
+    __shared__ double fold[kThreads / 64 - 1][3][VEC][64];
     const int b = blockIdx.z;
     const int rb = blockIdx.y;
-    const int64_t c0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * VEC;
-    if (c0 >= cols) return;
-    const int64_t r0 = (int64_t)rb * rb_rows;
-    const int64_t r1 = r0 + rb_rows < rows ? r0 + rb_rows : rows;
+    const int lane = threadIdx.x & 63, wave = WIDE ? 0 : threadIdx.x >> 6;
+    const int64_t c0 = ((int64_t)blockIdx.x * (WIDE ? kThreads : 64) + (WIDE ? threadIdx.x : lane)) * VEC;
+    const bool in = c0 < cols;
+    const int64_t quarter = rb_rows / kW;
+    const int64_t r0 = (int64_t)rb * rb_rows + wave * quarter;
+    const int64_t r1 = r0 + quarter < rows ? r0 + quarter : rows;
     const float* __restrict__ M = ms.m(b);
     const GT* __restrict__ G = ms.g<GT>(b);
+    typedef typename std::conditional<VEC == 4, float4, float>::type MRaw;
+    typedef typename std::conditional<VEC == 4, typename std::conditional<sizeof(GT) == 2, uint2, float4>::type,
+                                      GT>::type GRaw;
     double hi[VEC], lo[VEC], s2[VEC];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) hi[v] = lo[v] = s2[v] = 0.0;
-#pragma unroll 4
-    for (int64_t r = r0; r < r1; ++r) {
-        const float* p = M + r * cols + c0;
-        const GT* q = G + r * cols + c0;
+    auto add = [&](const MRaw& mr, const GRaw& gr) {
+        float m[VEC], g[VEC];
         if constexpr (VEC == 4) {
-            float m[4], g[4];
-            unpack4(ldg_nt<float4>(p), m);
-            unpack4(ldg_nt<typename std::conditional<sizeof(GT) == 2, uint2, float4>::type>(q), g);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) m[v] = m[v] + g[v];
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) accumulate(fabs((double)m[v]), hi[v], lo[v], s2[v]);
+            unpack4(mr, m);
+            unpack4(gr, g);
         } else {
-            const float m = ldg<float>(p) + Elem<GT>::load(q);
-            accumulate(fabs((double)m), hi[0], lo[0], s2[0]);
+            m[0] = mr;
+            if constexpr (sizeof(GT) == 2) g[0] = bf16_bits_to_f32(gr);
+            else g[0] = gr;
+        }
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) accumulate(fabs((double)(m[v] + g[v])), hi[v], lo[v], s2[v]);
+    };
+    if (in) {
+        int64_t r = r0;
+        for (; r + kColUnroll <= r1; r += kColUnroll) {
+            MRaw m[kColUnroll];
+            GRaw g[kColUnroll];
+#pragma unroll
+            for (int u = 0; u < kColUnroll; ++u) {
+                m[u] = ldg_nt<MRaw>(M + (r + u) * cols + c0);
+                g[u] = ldg_nt<GRaw>(G + (r + u) * cols + c0);
+            }
+#pragma unroll
+            for (int u = 0; u < kColUnroll; ++u) add(m[u], g[u]);
+        }
+        for (; r < r1; ++r) add(ldg_nt<MRaw>(M + r * cols + c0), ldg_nt<GRaw>(G + r * cols + c0));
+    }
+    if (wave > 0) {
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) {
+            fold[wave - 1][0][v][lane] = hi[v];
+            fold[wave - 1][1][v][lane] = lo[v];
+            fold[wave - 1][2][v][lane] = s2[v];
         }
     }
+    if constexpr (!WIDE) __syncthreads();
+    if (wave > 0 || !in) return;
     double* out = part + ((int64_t)b * nrb + rb) * 3 * cols;
 #pragma unroll
     for (int v = 0; v < VEC; ++v) {
+#pragma unroll
+        for (int w = 0; w < kW - 1; ++w) {
+            dd_add(hi[v], lo[v], fold[w][0][v][lane], fold[w][1][v][lane]);
+            s2[v] += fold[w][2][v][lane];
+        }
         out[c0 + v] = hi[v];
         out[cols + c0 + v] = lo[v];
         out[2 * cols + c0 + v] = s2[v];
     }
 }
 
+// The row blocks folded in order: a block takes 16 columns, sixteen groups of
+// threads a contiguous share of the row blocks each, and the shares are
+// folded in order. Latency-bound: one thread a column over 32 row blocks took
+// 12 us.
+constexpr int kFoldCols = 16;
+constexpr int kFoldWays = kThreads / kFoldCols;
+
 __global__ __launch_bounds__(kThreads) void momentum_cols_final(const double* __restrict__ part,
                                                                 int nrb, int64_t cols,
                                                                 double* __restrict__ l1,
                                                                 double* __restrict__ sq) {
+    __shared__ double fold[3][kFoldWays][kFoldCols];
     const int b = blockIdx.y;
-    const int64_t c = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (c >= cols) return;
+    const int cl = threadIdx.x % kFoldCols, way = threadIdx.x / kFoldCols;
+    const int64_t c = (int64_t)blockIdx.x * kFoldCols + cl;
+    const int per = (nrb + kFoldWays - 1) / kFoldWays;
+    const int q0 = way * per < nrb ? way * per : nrb;
+    const int q1 = q0 + per < nrb ? q0 + per : nrb;
     double hi = 0.0, lo = 0.0, s2 = 0.0;
-    for (int rb = 0; rb < nrb; ++rb) {
-        const double* p = part + ((int64_t)b * nrb + rb) * 3 * cols;
-        dd_add(hi, lo, p[c], p[cols + c]);
-        s2 += p[2 * cols + c];
+    if (c < cols) {
+        const double* p = part + ((int64_t)b * nrb + q0) * 3 * cols + c;
+#pragma unroll 4
+        for (int rb = q0; rb < q1; ++rb, p += 3 * cols) {
+            dd_add(hi, lo, p[0], p[cols]);
+            s2 += p[2 * cols];
+        }
+    }
+    fold[0][way][cl] = hi;
+    fold[1][way][cl] = lo;
+    fold[2][way][cl] = s2;
+    __syncthreads();
+    if (way > 0 || c >= cols) return;
+    for (int w = 1; w < kFoldWays; ++w) {
+        dd_add(hi, lo, fold[0][w][cl], fold[1][w][cl]);
+        s2 += fold[2][w][cl];
     }
     l1[(int64_t)b * cols + c] = hi + lo;
     sq[(int64_t)b * cols + c] = s2;
@@ -177,20 +244,20 @@ hipError_t launch_typed(const MomentumArgs& a, int axis, hipStream_t s) {
         hipLaunchKernelGGL((momentum_rows<VEC, GT>), grid, dim3(kThreads), 0, s, a.ms, a.rows,
                            a.cols, a.l1, a.sq);
     } else {
-        // Blocks of four waves where they tile the row exactly, else of one
-        // wave, so a row that is not a multiple of 256 * VEC columns wide
-        // leaves at most part of one wave idle (1408 columns: 8% of the
-        // lanes instead of 31%). Each column's rows are summed in the same
-        // order either way.
-        const int threads = a.cols % ((int64_t)kThreads * VEC) == 0 ? kThreads : 64;
-        const int64_t per_block = (int64_t)threads * VEC;
+        const bool wide = a.cols % ((int64_t)kThreads * VEC) == 0 &&
+                          a.cols / (kThreads * VEC) * a.nrb * a.batch >= 1024;
+        const int64_t per_block = (wide ? kThreads : 64) * VEC;
         dim3 grid((unsigned)((a.cols + per_block - 1) / per_block), (unsigned)a.nrb,
                   (unsigned)a.batch);
-        hipLaunchKernelGGL((momentum_cols_partial<VEC, GT>), grid, dim3(threads), 0, s, a.ms,
-                           a.rows, a.cols, a.rb_rows, a.nrb, a.part);
+        if (wide)
+            hipLaunchKernelGGL((momentum_cols_partial<VEC, GT, true>), grid, dim3(kThreads), 0, s, a.ms,
+                               a.rows, a.cols, a.rb_rows, a.nrb, a.part);
+        else
+            hipLaunchKernelGGL((momentum_cols_partial<VEC, GT, false>), grid, dim3(kThreads), 0, s, a.ms,
+                               a.rows, a.cols, a.rb_rows, a.nrb, a.part);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        dim3 grid2((unsigned)((a.cols + kThreads - 1) / kThreads), (unsigned)a.batch);
+        dim3 grid2((unsigned)((a.cols + kFoldCols - 1) / kFoldCols), (unsigned)a.batch);
         hipLaunchKernelGGL(momentum_cols_final, grid2, dim3(kThreads), 0, s, a.part, a.nrb,
                            a.cols, a.l1, a.sq);
     }
@@ -200,12 +267,19 @@ hipError_t launch_typed(const MomentumArgs& a, int axis, hipStream_t s) {
 }  // namespace
 
 // Row blocking of the column-mode reduction: blocks of 256 rows keep the
-// partials small next to the matrix while giving enough blocks to fill the
-// chip.
-int64_t momentum_col_blocks(int64_t rows, int* rb_rows) {
-    const int rb = 256;
+// partials small next to the matrix (24 bytes for 1280 or more); a launch
+// of fewer than four blocks a compute unit halves them, down to 32 rows, as
+// long as the partials fit in part_bytes.
+int64_t momentum_col_blocks(int64_t rows, int64_t cols, int batch, size_t part_bytes, int* rb_rows) {
+    const int64_t vec = cols % 4 == 0 ? 4 : 1;
+    const int64_t strips = (cols + 64 * vec - 1) / (64 * vec) * batch;
+    auto blocks = [&](int rb) { return (rows + rb - 1) / rb; };
+    int rb = 256;
+    while (rb > 32 && strips * blocks(rb) < 1024 &&
+           (size_t)batch * (size_t)blocks(rb / 2) * 3 * (size_t)cols * sizeof(double) <= part_bytes)
+        rb /= 2;
     *rb_rows = rb;
-    return (rows + rb - 1) / rb;
+    return blocks(rb);
 }
 
 hipError_t launch_momentum(const MomentumArgs& a, int axis, int g_bf16, hipStream_t s) {

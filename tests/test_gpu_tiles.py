@@ -12,7 +12,7 @@ import pytest
 import torch
 
 from paper_2512_16928_amd import binding, workloads
-from paper_2512_16928_amd.binding import AXIS_AUTO, CHAIN_F16, MASTER_FP32, NS_DIRECT, NS_GRAM, SELECT_RANDOM
+from paper_2512_16928_amd.binding import AXIS_AUTO, AXIS_COLS, CHAIN_F16, MASTER_FP32, NS_DIRECT, NS_GRAM, SELECT_RANDOM
 from test_gpu_parity import check_matrix, one_group_workload, run_gpu
 
 pytestmark = pytest.mark.gpu
@@ -25,11 +25,11 @@ def nan_workspace(batch, rows, cols, alpha, device, **kw):
 
 @pytest.mark.parametrize("rows,cols,alpha,batches,kw", [
     (260, 1030, 0.25, (1, 2, 90), {}),                           # s = 65: one 64-tile more than s fills
-    (1030, 516, 0.5, (1, 25, 26, 71), dict(ns_form=NS_GRAM)),    # s = 258, columns: 15 tiles, 375 and 390 blocks
-    (1000, 1000, 0.25, (1, 25, 26, 70, 71), dict(ns_form=NS_GRAM)),   # s = 250: 250, 260, 700 and 710 blocks
+    (1030, 516, 0.5, (1, 17, 18, 38), dict(ns_form=NS_GRAM)),    # s = 258, columns: 15 tiles each, 255 to 570 blocks
+    (1000, 1000, 0.25, (1, 25, 26, 56, 57), dict(ns_form=NS_GRAM)),   # s = 250: 250, 260, 560 and 570 blocks
     (640, 1000, 0.5, (1, 12, 17), dict(ns_form=NS_DIRECT)),      # s = 320: one-pass products at 252 and 357 blocks
     (450, 700, 1.0, (1, 8, 13), {}),                             # s = 450, DIRECT, 448 sides written of 512
-    (960, 960, 0.25, (1, 26, 71), dict(ns_master=MASTER_FP32)),   # K = 960: the three-pass Gram splits from 1024
+    (960, 960, 0.25, (1, 26, 57), dict(ns_master=MASTER_FP32)),   # K = 960: the three-pass Gram splits from 1024
     (516, 1030, 0.25, (1, 86), dict(ns_chain=CHAIN_F16)),        # s = 129, l = 8 s: fp16 products
 ])
 def test_tiles_bitwise_across_batches(hip_device, rows, cols, alpha, batches, kw):
@@ -70,3 +70,24 @@ def test_split_k(hip_device, rows, cols, alpha, batch, kw, tol):
     binding.dion2_step_ex(W2, M2, G, alpha, workspace=ws, **kw)
     torch.cuda.synchronize()
     assert torch.equal(W2.cpu().view(torch.int16), res["W"].view(torch.int16)) and torch.equal(M2.cpu(), res["M"])
+
+
+@pytest.mark.parametrize("rows,cols,batch", [
+    (8192, 132, 1),     # one narrow strip: 32-row blocks, shortest allowed
+    (1000, 771, 2),     # scalar columns, a last block of 8 rows (waves without rows)
+    (290, 2048, 1),     # columns by request on a wide matrix: a second block of 34 rows
+    (4096, 1024, 64),   # wide blocks
+    (4097, 1024, 65),   # wide blocks, a last block of one row
+])
+@pytest.mark.parametrize("gdt", ["bf16", "f32"])
+def test_column_norm_blocks(hip_device, rows, cols, batch, gdt):
+    """Row blocking and waves of the column norms: exact l1 norms, selection
+    and momentum in each, on the smallest compact matrix (the partials share
+    its memory)."""
+    wl = one_group_workload(rows, cols, axis=AXIS_COLS, name=f"cols{rows}x{cols}")
+    W, M, G = workloads.make_group(wl, 0, hip_device)
+    G = G.float() if gdt == "f32" else G
+    Wn, Mn, Gn = (t.repeat(batch, 1, 1) for t in (W, M, G))
+    res = run_gpu(Wn, Mn, Gn, 0.02, axis=AXIS_COLS, ns_steps=1)
+    check_matrix(res, batch - 1, 0.02, ns_steps=1, axis=AXIS_COLS)
+    assert bool((res["norms"] == res["norms"][0]).all())
