@@ -509,6 +509,7 @@ GemmArgs right_args(const Plan& P, const uint16_t* xh, const uint16_t* xl, const
     x.K = (int)P.s_k;
     x.lda = (int)P.s_pad;
     x.ldb = (int)P.l_pad;
+    x.mreal = (int)round_up(P.s_k, 64);
     return x;
 }
 

@@ -313,9 +313,10 @@ struct GemmArgs {
     // fp16 Gram-form chain: fp16 operands, and the scale exponents above
     int f16;
     int oexp, oexpx, eexp, sexp;
-    // symmetric products: the side their output is needed to (a multiple of
-    // 64; 0: all of M). Tiles past it may be left unwritten: nothing in them
-    // reaches a real entry, since every sum over s stops there.
+    // the rows (of a symmetric product also the columns) the output is needed
+    // to, a multiple of 64 (0: all of M). Tiles past them may be left
+    // unwritten: nothing in them reaches a real entry, since every sum over s
+    // stops there.
     int mreal;
     // symmetric products whose K launch_gemm may split: scratch of part_floats
     // fp32 values for the partial sums (null: never split), and the parts
@@ -336,8 +337,8 @@ int gemm_launches(const GemmArgs& a, GemmEpi epi, int npass);
 
 // The GRAM form's chain of s x s products for s <= 64 (s_k, the K extent,
 // 32 or 64) in one launch, one block per matrix: A_0 in, P_T out, both as
-// bf16 hi / lo pairs [batch][s_pad][s_pad]; P_T is zero outside
-// [0, s_k)^2. Every product is computed as the launch-per-product chain
+// bf16 hi / lo pairs [batch][s_pad][s_pad], of which [0, s_k)^2 is read and
+// written. Every product is computed as the launch-per-product chain
 // computes it, so P_T is bitwise that chain's on [0, s_k)^2.
 constexpr int kSmallChainS = 64;
 constexpr int kChainMaxSteps = 16;   // DION2_MAX_NS_STEPS

@@ -770,140 +770,175 @@ __global__ __launch_bounds__(256) void reduce_parts(GemmArgs a) {
 // makes: per 16-deep k-step hi*lo, lo*hi, then hi*hi into fp32
 // accumulators, the same epilogue arithmetic and hi / lo split, and exactly
 // symmetric storage (entries on and above the diagonal computed, mirrored
-// below it). Waves 0..2 take the upper 32 x 32 blocks (0,0), (0,1), (1,1);
-// with s_k = 32 (KS) only the first. Entries past s_k are never read.
+// below it). Entries past s_k are never read.
+//
+// Bound by latency: fourteen dependent stages of one to two products, each
+// 12 dependent MFMAs between LDS reads and writes. So the code is one
+// product's (a second copy would be fetched cold into the instruction cache
+// of a kernel that runs once), a stage's two products go to different waves,
+// and the stores are 8 bytes wide where a lane holds four entries of a row:
+// 28.0 us before, with separate copies and 2-byte stores, 16.2 us now (five
+// steps, s = 64).
 constexpr int kSmallPitch = 72;
 constexpr int kSmallPlane = kSmallChainS * kSmallPitch;
 enum { SP_A = 0, SP_Q = 2, SP_T = 4, SP_P = 6, SP_PLANES = 10 };   // hi, lo; P twice (6 and 8)
 
-// dst[p] = x y[p] (x, y[p] symmetric, given by rows) on this wave's block
-// (bi, bj), for NP products sharing x; their MFMA chains interleave, each in
-// its own order. With QPOLY (NP = 1, x = y = A_t) dst = c x y + b x + a I:
-// Q_t.
-template <int KS, int NP, bool QPOLY>
-__device__ __forceinline__ void small_products(uint16_t* pl, int x, const int (&y)[NP], const int (&dst)[NP],
-                                               int bi, int bj, int lane, float ca, float cb, float cc) {
-    static_assert(!QPOLY || NP == 1, "the polynomial epilogue takes one product");
+// dst = x y (x, y symmetric, given by rows) on the 32 x 32 block of rows
+// bi and columns bj, by one wave; qpoly: dst = c x y + b x + a I (x = y =
+// A_t). An MFMA lane holds one column's entries of four row quads, that is
+// 8-byte pieces of the mirrored block's rows. Of the block above the diagonal
+// one wave computes it and stores the mirror, and another computes the
+// transposed block (operands swapped, bitwise the same sums) and stores it
+// (`swap`). A block on the diagonal is stored mirrored whole, then its
+// entries above the diagonal are stored over it.
+// The fragments of x stay in xh, xl: `fresh` says that x is another one, or
+// the same plane rewritten.
+template <int KS>
+__device__ __forceinline__ void small_product(uint16_t* pl, int x, int y, int dst, bool qpoly, int bi, int bj,
+                                              bool swap, int lane, float ca, float cb, float cc, bool fresh,
+                                              bf16x8 (&xh)[KS / 16], bf16x8 (&xl)[KS / 16]) {
     constexpr int NK = KS / 16;
-    const uint16_t* xh = pl + x * kSmallPlane;
-    const uint16_t* xl = xh + kSmallPlane;
-    const int arow = bi * 32 + (lane & 31), brow = bj * 32 + (lane & 31);
-    const int half = lane >> 5;
-    auto entry = [&](int r, int& m, int& n) {
-        m = bi * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-        n = bj * 32 + (lane & 31);
-    };
-    // the epilogue's A entries (QPOLY) and every fragment first, then the MFMAs
-    float a0[16];
-    if constexpr (QPOLY) {
+    const uint16_t* xr = pl + x * kSmallPlane + (bi * 32 + (lane & 31)) * kSmallPitch + 8 * (lane >> 5);
+    const uint16_t* yr = pl + y * kSmallPlane + (bj * 32 + (lane & 31)) * kSmallPitch + 8 * (lane >> 5);
+    bf16x8 yh[NK], yl[NK];
+    if (fresh) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            int m, n;
-            entry(r, m, n);
-            a0[r] = bf16_bits_to_f32(xh[m * kSmallPitch + n]) + bf16_bits_to_f32(xl[m * kSmallPitch + n]);
+        for (int k = 0; k < NK; ++k) {
+            xh[k] = *reinterpret_cast<const bf16x8*>(xr + 16 * k);
+            xl[k] = *reinterpret_cast<const bf16x8*>(xr + kSmallPlane + 16 * k);
         }
     }
-    bf16x8 ah[NK], al[NK], bh[NP][NK], bl[NP][NK];
 #pragma unroll
     for (int k = 0; k < NK; ++k) {
-        const int kc = 16 * k + 8 * half;
-        ah[k] = *reinterpret_cast<const bf16x8*>(xh + arow * kSmallPitch + kc);
-        al[k] = *reinterpret_cast<const bf16x8*>(xl + arow * kSmallPitch + kc);
+        yh[k] = *reinterpret_cast<const bf16x8*>(yr + 16 * k);
+        yl[k] = *reinterpret_cast<const bf16x8*>(yr + kSmallPlane + 16 * k);
+    }
+    // where this lane's entries go: row n, columns m0 + 8 q .. m0 + 8 q + 3
+    const int n = (swap ? bi : bj) * 32 + (lane & 31);
+    const int m0 = (swap ? bj : bi) * 32 + 4 * (lane >> 5);
+    const int at = n * kSmallPitch + m0;
+    uint2 eh[4], el[4];   // A there (it is symmetric)
+    if (qpoly) {
+        const uint16_t* xp = pl + x * kSmallPlane + at;
 #pragma unroll
-        for (int p = 0; p < NP; ++p) {
-            const uint16_t* yh = pl + y[p] * kSmallPlane;
-            bh[p][k] = *reinterpret_cast<const bf16x8*>(yh + brow * kSmallPitch + kc);
-            bl[p][k] = *reinterpret_cast<const bf16x8*>(yh + kSmallPlane + brow * kSmallPitch + kc);
+        for (int q = 0; q < 4; ++q) {
+            eh[q] = *reinterpret_cast<const uint2*>(xp + 8 * q);
+            el[q] = *reinterpret_cast<const uint2*>(xp + kSmallPlane + 8 * q);
         }
     }
-    f32x16 acc[NP];
+    f32x16 acc;
 #pragma unroll
-    for (int p = 0; p < NP; ++p)
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    if (swap) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[p][r] = 0.f;
+        for (int k = 0; k < NK; ++k) {
+            acc = mfma32(yl[k], xh[k], acc);
+            acc = mfma32(yh[k], xl[k], acc);
+            acc = mfma32(yh[k], xh[k], acc);
+        }
+    } else {
 #pragma unroll
-    for (int k = 0; k < NK; ++k) {
-#pragma unroll
-        for (int p = 0; p < NP; ++p) acc[p] = mfma32(ah[k], bl[p][k], acc[p]);
-#pragma unroll
-        for (int p = 0; p < NP; ++p) acc[p] = mfma32(al[k], bh[p][k], acc[p]);
-#pragma unroll
-        for (int p = 0; p < NP; ++p) acc[p] = mfma32(ah[k], bh[p][k], acc[p]);
+        for (int k = 0; k < NK; ++k) {
+            acc = mfma32(xh[k], yl[k], acc);
+            acc = mfma32(xl[k], yh[k], acc);
+            acc = mfma32(xh[k], yh[k], acc);
+        }
     }
+    if (qpoly) {
 #pragma unroll
-    for (int p = 0; p < NP; ++p) {
-        uint16_t* oh = pl + dst[p] * kSmallPlane;
-        uint16_t* ol = oh + kSmallPlane;
+        for (int q = 0; q < 4; ++q) {
+            float a0[4], a1[4];
+            unpack4(eh[q], a0);
+            unpack4(el[q], a1);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            int m, n;
-            entry(r, m, n);
-            if (bi == bj && m > n) continue;   // below the diagonal: the mirror of (n, m)
-            float v = acc[p][r];
-            if constexpr (QPOLY) {
-                v = cb * a0[r] + cc * v;
-                if (m == n) v += ca;
+            for (int u = 0; u < 4; ++u) {
+                float v = cb * (a0[u] + a1[u]) + cc * acc[4 * q + u];
+                if (m0 + 8 * q + u == n) v += ca;
+                acc[4 * q + u] = v;
             }
-            const uint16_t h = f32_to_bf16(v);
-            const uint16_t l = (uint16_t)(pack2(v - bf16_bits_to_f32(h), 0.f) & 0xffffu);
-            oh[m * kSmallPitch + n] = h;
-            ol[m * kSmallPitch + n] = l;
-            if (m != n) {
-                oh[n * kSmallPitch + m] = h;
-                ol[n * kSmallPitch + m] = l;
+        }
+    }
+    uint16_t* oh = pl + dst * kSmallPlane;
+    uint2 h[4], l[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        h[q] = make_uint2(pack2(acc[4 * q], acc[4 * q + 1]), pack2(acc[4 * q + 2], acc[4 * q + 3]));
+        float hf[4];
+        unpack4(h[q], hf);
+        l[q] = make_uint2(pack2(acc[4 * q] - hf[0], acc[4 * q + 1] - hf[1]),
+                          pack2(acc[4 * q + 2] - hf[2], acc[4 * q + 3] - hf[3]));
+        *reinterpret_cast<uint2*>(oh + at + 8 * q) = h[q];
+        *reinterpret_cast<uint2*>(oh + kSmallPlane + at + 8 * q) = l[q];
+    }
+    if (bi == bj) {
+        // LDS accesses of one wave complete in issue order. Lanes at or below
+        // the diagonal store into their row's padding instead of branching.
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t hw[2] = {h[q].x, h[q].y}, lw[2] = {l[q].x, l[q].y};
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int m = m0 + 8 * q + u;
+                uint16_t* o = oh + (m < n ? m * kSmallPitch + n : n * kSmallPitch + kSmallChainS);
+                o[0] = (uint16_t)(hw[u >> 1] >> (16 * (u & 1)));
+                o[kSmallPlane] = (uint16_t)(lw[u >> 1] >> (16 * (u & 1)));
             }
         }
     }
 }
 
+// Waves 0 .. 3 compute a stage's first product (blocks (0,0), (1,1), (0,1)
+// and its transposed twin; with KS = 32 wave 0 alone), waves 4 .. 7 its second.
+constexpr int kSmallThreads = 512;
+
 template <int KS>
-__global__ __launch_bounds__(256) void chain_small(SmallChainArgs a) {
+__global__ __launch_bounds__(kSmallThreads) void chain_small(SmallChainArgs a) {
     __shared__ __attribute__((aligned(16))) uint16_t pl[SP_PLANES * kSmallPlane];
     const int b = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t s2 = a.s_pad * a.s_pad;
-    // A_0's [0, 64)^2 corner (zero past s_k) into the A planes, 16 bytes a lane
-    constexpr int kChunks = kSmallChainS * (kSmallChainS / 8);   // per plane
-    for (int i = tid; i < 2 * kChunks; i += 256) {
-        const int plane = i / kChunks, r = (i % kChunks) / 8, c = i % 8;
+    constexpr int kChunks = KS * (KS / 8);   // 16-byte pieces of [0, KS)^2, per plane
+    for (int i = tid; i < 2 * kChunks; i += kSmallThreads) {
+        const int plane = i / kChunks, r = (i % kChunks) / (KS / 8), c = i % (KS / 8);
         const uint16_t* src = (plane ? a.Al : a.Ah) + (int64_t)b * s2 + (int64_t)r * a.s_pad + 8 * c;
         *reinterpret_cast<uint4*>(pl + (SP_A + plane) * kSmallPlane + r * kSmallPitch + 8 * c) = ldg<uint4>(src);
     }
     __syncthreads();
-    const int bi = wave == 2 ? 1 : 0, bj = wave == 0 ? 0 : 1;
-    const bool active = wave == 0 || (KS > 32 && wave < 3);
+    const int w = wave & 3, second = wave >> 2;
+    const int bi = w == 1 ? 1 : 0, bj = w == 0 ? 0 : 1;
+    const bool mine = KS > 32 || w == 0;
     int cur = 0;
+    bf16x8 xh[KS / 16], xl[KS / 16];
+    // per step: Q_t (the first one is P itself); T = Q_t A (t < T - 1) and
+    // P <- Q_t P (t > 0); A <- Q_t T (t < T - 1)
     for (int t = 0; t < a.ns_steps; ++t) {
         const float ca = a.cf[t][0], cb = a.cf[t][1], cc = a.cf[t][2];
-        const int q = t == 0 ? SP_P : SP_Q;   // the first Q_t is P itself
-        if (active) small_products<KS, 1, true>(pl, SP_A, {SP_A}, {q}, bi, bj, lane, ca, cb, cc);
-        __syncthreads();
-        // P <- Q_t P (t > 0) and T = Q_t A (t < T - 1), then A <- Q_t T
         const bool do_p = t > 0, do_t = t + 1 < a.ns_steps;
-        const int pin = SP_P + 2 * cur, pout = SP_P + 2 * (1 - cur);
-        if (active) {
-            if (do_p && do_t) small_products<KS, 2, false>(pl, q, {pin, SP_A}, {pout, SP_T}, bi, bj, lane, 0.f, 0.f, 0.f);
-            else if (do_p) small_products<KS, 1, false>(pl, q, {pin}, {pout}, bi, bj, lane, 0.f, 0.f, 0.f);
-            else if (do_t) small_products<KS, 1, false>(pl, q, {SP_A}, {SP_T}, bi, bj, lane, 0.f, 0.f, 0.f);
-        }
-        __syncthreads();
-        if (do_p) cur = 1 - cur;
-        if (do_t) {
-            if (active) small_products<KS, 1, false>(pl, q, {SP_T}, {SP_A}, bi, bj, lane, 0.f, 0.f, 0.f);
+        const int q = t == 0 ? SP_P : SP_Q;
+        // the second stage's second product, and whether it is due
+        const int y1 = second ? SP_P + 2 * cur : SP_A, dst1 = second ? SP_P + 2 * (1 - cur) : SP_T;
+        const bool due1 = second ? do_p : do_t;
+        const int stages = do_t ? 3 : 2;
+#pragma unroll 1
+        for (int stage = 0; stage < stages; ++stage) {
+            const int x = stage == 0 ? SP_A : q;
+            const int y = stage == 0 ? SP_A : stage == 1 ? y1 : SP_T;
+            const int dst = stage == 0 ? q : stage == 1 ? dst1 : SP_A;
+            if (mine && (stage == 1 ? due1 : !second))
+                small_product<KS>(pl, x, y, dst, stage == 0, bi, bj, w == 3, lane, ca, cb, cc, stage < 2, xh,
+                                  xl);   // the third stage's x is the second's
             __syncthreads();
         }
+        if (do_p) cur = 1 - cur;
     }
-    // P_T out: [0, s_k)^2 from LDS, zero elsewhere
+    // P_T out
     const uint16_t* ph = pl + (SP_P + 2 * cur) * kSmallPlane;
-    const int64_t cpr = a.s_pad / 8;   // 16-byte chunks per row
-    for (int64_t i = tid; i < 2 * a.s_pad * cpr; i += 256) {
-        const int plane = (int)(i / (a.s_pad * cpr));
-        const int64_t rem = i % (a.s_pad * cpr);
-        const int64_t r = rem / cpr, c = rem % cpr;
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (r < KS && 8 * c < KS) v = *reinterpret_cast<const uint4*>(ph + plane * kSmallPlane + r * kSmallPitch + 8 * c);
-        stg((plane ? a.Pl : a.Ph) + (int64_t)b * s2 + r * a.s_pad + 8 * c, v);
+    for (int i = tid; i < 2 * kChunks; i += kSmallThreads) {
+        const int plane = i / kChunks, r = (i % kChunks) / (KS / 8), c = i % (KS / 8);
+        stg((plane ? a.Pl : a.Ph) + (int64_t)b * s2 + (int64_t)r * a.s_pad + 8 * c,
+            *reinterpret_cast<const uint4*>(ph + plane * kSmallPlane + r * kSmallPitch + 8 * c));
     }
 }
 
@@ -1126,6 +1161,7 @@ hipError_t launch_right(const GemmArgs& a, hipStream_t s) {
         using T = Tile<NPASS, 1, 64, 128, NPASS == 1 ? 64 : kSliceK, 2, 4, NPASS == 1 ? 3 : 4>;
         GemmArgs r = a;
         r.K = (a.K + T::BK - 1) / T::BK * T::BK;   // operands are zero to the next 64
+        if (a.mreal) r.M = a.mreal;
         return launch_tile<NPASS, EPI, T>(r, s);
     }
     if constexpr (NPASS == 2 && EPI == EPI_APPLY)
@@ -1210,8 +1246,8 @@ hipError_t launch_chain_small(const SmallChainArgs& a, hipStream_t s) {
     if (a.s_k < 32 || a.s_k > kSmallChainS || a.s_k % 32 || a.s_pad < kSmallChainS || a.s_pad % 8 ||
         a.ns_steps < 1 || a.ns_steps > kChainMaxSteps || a.batch < 1)
         return hipErrorInvalidValue;
-    if (a.s_k == 32) hipLaunchKernelGGL(chain_small<32>, dim3((unsigned)a.batch), dim3(256), 0, s, a);
-    else hipLaunchKernelGGL(chain_small<64>, dim3((unsigned)a.batch), dim3(256), 0, s, a);
+    if (a.s_k == 32) hipLaunchKernelGGL(chain_small<32>, dim3((unsigned)a.batch), dim3(kSmallThreads), 0, s, a);
+    else hipLaunchKernelGGL(chain_small<64>, dim3((unsigned)a.batch), dim3(kSmallThreads), 0, s, a);
     return hipGetLastError();
 }
 
