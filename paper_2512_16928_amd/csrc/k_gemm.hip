@@ -91,14 +91,19 @@ __device__ __forceinline__ f32x16 mfma32(f16x8 a, f16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
 }
 
-template <int NPASS, int BT_, int BM_, int BN_, int BK_, int WM_, int WN_, int S_, bool F16_ = false>
+template <int NPASS, int BT_, int BM_, int BN_, int BK_, int WM_, int WN_, int S_, bool F16_ = false,
+          bool PIPE_ = (BM_ * BN_ > 64 * 128 && !BT_ && !(NPASS == 3 && BM_ == 128))>
 struct Tile {
+    static constexpr bool PIPE = PIPE_;                  // the k-steps run on over slice ends (see gemm)
     static constexpr int BT = BT_, S = S_;
     static constexpr bool F16 = F16_;                    // fp16 operands (else bf16)
     using Frag = typename std::conditional<F16_, f16x8, bf16x8>::type;
     static constexpr int BM = BM_, BN = BN_, BK = BK_, WM = WM_, WN = WN_;
     static constexpr int WAVES = WM * WN;
     static constexpr int THREADS = 64 * WAVES;
+    // waves per SIMD to leave registers for: two blocks of eight waves a CU
+    // up to 128 x 128 (a polynomial epilogue is two registers over without)
+    static constexpr int MIN_WAVES = WAVES == 8 && BM * BN <= 128 * 128 ? 4 : 1;
     static constexpr int TM = BM / WM, TN = BN / WN;     // wave tile
     static constexpr int FM = TM / 32, FN = TN / 32;     // MFMA blocks per wave
     static constexpr int NA = NPASS == 1 ? 1 : 2;        // A operand tiles (hi[, lo])
@@ -137,48 +142,62 @@ __device__ __forceinline__ int nmajor_off(int r, int c) {
     return r * 256 + 16 * (c ^ ((r & 3) << 2));
 }
 
-// Issue the direct-to-LDS load `q` (0 <= q < IPW) of this wave's part of
-// K-slice `kt` into the stage at `dst`. Wave w owns the stage's 1 KB blocks
-// w, w + WAVES, ...; lane i of a block fills the block's 16-byte slot i with
-// the global chunk that belongs there.
-template <int NPASS, typename T>
-__device__ __forceinline__ void load_one(const GemmArgs& a, unsigned char* dst, int kt,
-                                         const uint16_t* const (&abase)[2],
-                                         const uint16_t* const (&bbase)[2], int wave, int lane, int q) {
-    const int blk = wave + q * T::WAVES;   // 1 KB block of the stage (wave-uniform)
-    const uint16_t* src;
-    if (blk * 1024 < T::NA * T::A_BYTES) {
-        // K-major A tile: the block holds 1024 / PK whole rows
-        const int t = (blk * 1024) / T::A_BYTES;
-        const int lb = (blk * 1024) % T::A_BYTES + lane * 16;
-        const int r = lb / T::PK, slot = (lb % T::PK) / 16;
-        const int c = slot ^ ((r / T::GK) % T::CPR);
-        src = (t ? abase[1] : abase[0]) + (int64_t)r * a.lda + (int64_t)kt * T::BK + c * 8;
-    } else {
-        const int bb = blk * 1024 - T::NA * T::A_BYTES;
-        const int t = bb / T::B_BYTES;
-        const int lb = bb % T::B_BYTES + lane * 16;
-        if constexpr (T::BT) {
-            const int r = lb / 256, slot = (lb % 256) / 16;
-            const int c = slot ^ ((r & 3) << 2);
-            src = (t ? bbase[1] : bbase[0]) + ((int64_t)kt * T::BK + r) * a.ldb + c * 8;
-        } else {
-            const int r = lb / T::PK, slot = (lb % T::PK) / 16;
-            const int c = slot ^ ((r / T::GK) % T::CPR);
-            src = (t ? bbase[1] : bbase[0]) + (int64_t)r * a.ldb + (int64_t)kt * T::BK + c * 8;
+// This wave's part of the operands' K-slices. Wave w owns a stage's 1 KB
+// blocks w, w + WAVES, ...; lane i of a block fills the block's 16-byte slot
+// i with the global chunk that belongs there. The operand's address is
+// uniform and moves on by one slice at a time; a lane's offset from it is
+// fixed, so a load in the loop costs scalar work alone.
+template <typename T>
+struct Loader {
+    const unsigned char* base[T::IPW];
+    uint32_t off[T::IPW];
+    int64_t b_step;   // bytes between slices of the [K][N] B operand (rows: PK)
+
+    // a0, a1 (b0, b1): the tile's first row (column) of the operands, in the
+    // first slice; ops no larger than 2^31 bytes from there (a tile's rows)
+    __device__ __forceinline__ void init(const GemmArgs& a, const uint16_t* a0, const uint16_t* a1,
+                                         const uint16_t* b0, const uint16_t* b1, int wave, int lane) {
+        b_step = T::BT ? (int64_t)T::BK * a.ldb * 2 : T::PK;
+#pragma unroll
+        for (int q = 0; q < T::IPW; ++q) {
+            const int blk = wave + q * T::WAVES;   // 1 KB block of the stage (wave-uniform)
+            if (blk * 1024 < T::NA * T::A_BYTES) {
+                // K-major A tile: the block holds 1024 / PK whole rows
+                const int t = (blk * 1024) / T::A_BYTES;
+                const int lb = (blk * 1024) % T::A_BYTES + lane * 16;
+                const int r = lb / T::PK, slot = (lb % T::PK) / 16;
+                const int c = slot ^ ((r / T::GK) % T::CPR);
+                base[q] = reinterpret_cast<const unsigned char*>(t ? a1 : a0);
+                off[q] = 2u * ((uint32_t)r * (uint32_t)a.lda + c * 8);
+            } else {
+                const int bb = blk * 1024 - T::NA * T::A_BYTES;
+                const int t = bb / T::B_BYTES;
+                const int lb = bb % T::B_BYTES + lane * 16;
+                base[q] = reinterpret_cast<const unsigned char*>(t ? b1 : b0);
+                if constexpr (T::BT) {
+                    const int r = lb / 256, slot = (lb % 256) / 16;
+                    const int c = slot ^ ((r & 3) << 2);
+                    off[q] = 2u * ((uint32_t)r * (uint32_t)a.ldb + c * 8);
+                } else {
+                    const int r = lb / T::PK, slot = (lb % T::PK) / 16;
+                    const int c = slot ^ ((r / T::GK) % T::CPR);
+                    off[q] = 2u * ((uint32_t)r * (uint32_t)a.ldb + c * 8);
+                }
+            }
         }
     }
-    __builtin_amdgcn_global_load_lds(src, (lds_void*)(dst + blk * 1024), 16, 0, 0);
-}
-
-// All of this wave's loads of K-slice `kt` (the ring's prologue).
-template <int NPASS, typename T>
-__device__ __forceinline__ void load_slice(const GemmArgs& a, unsigned char* dst, int kt,
-                                           const uint16_t* const (&abase)[2],
-                                           const uint16_t* const (&bbase)[2], int wave, int lane) {
+    __device__ __forceinline__ void load(int q, unsigned char* dst, int wave) const {
+        const unsigned char* src = base[q] + off[q];
+        __builtin_amdgcn_global_load_lds(src, (lds_void*)(dst + (wave + q * T::WAVES) * 1024), 16, 0, 0);
+    }
+    __device__ __forceinline__ void advance(int wave) {
 #pragma unroll
-    for (int q = 0; q < T::IPW; ++q) load_one<NPASS, T>(a, dst, kt, abase, bbase, wave, lane, q);
-}
+        for (int q = 0; q < T::IPW; ++q) {
+            const bool is_a = (wave + q * T::WAVES) * 1024 < T::NA * T::A_BYTES;
+            base[q] += !T::BT || is_a ? (int64_t)T::PK : b_step;
+        }
+    }
+};
 
 // Wait until at most N vector-memory loads of this wave are outstanding
 // (vmcnt only; lgkmcnt and expcnt left at their maxima).
@@ -186,6 +205,13 @@ template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
     static_assert(N >= 0 && N < 64, "vmcnt range");
     __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+}
+
+// The same, and every LDS read of this wave done.
+template <int N>
+__device__ __forceinline__ void wait_all_lds_vmcnt() {
+    static_assert(N >= 0 && N < 64, "vmcnt range");
+    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));
 }
 
 // B fragment (8 consecutive K of one column) from the [BK][BN] tile through
@@ -205,86 +231,71 @@ __device__ __forceinline__ bf16x8 b_frag_tr(const unsigned char* sb, int krow, i
     return __builtin_bit_cast(bf16x8, v);
 }
 
-// MFMAs of one BK-deep K-slice staged at `st`, fragments software-pipelined
-// (k-step kk+1 is read from LDS while the MFMAs of kk run). The loads of
-// slice `kn` into the stage at `ldst` are spread between the MFMAs, each
-// fenced in place: issued in one burst ahead of the MFMAs they hold the
-// wave in the vector-memory issue queue while its matrix pipe idles.
+// One k-step's fragments from the slice staged at `st`.
 template <int NPASS, typename T>
-__device__ __forceinline__ void mma_slice(f32x16 (&acc)[T::FM][T::FN], const unsigned char* st,
-                                          int wm, int wn, int lane, const GemmArgs& a, unsigned char* ldst,
-                                          int kn, const uint16_t* const (&abase)[2],
-                                          const uint16_t* const (&bbase)[2], int wave) {
-    const unsigned char* sa0 = st;
-    const unsigned char* sa1 = st + T::A_BYTES;
-    const unsigned char* sb0 = st + T::NA * T::A_BYTES;
-    const unsigned char* sb1 = sb0 + T::B_BYTES;
-    const int arow = wm * T::TM + (lane & 31);
-    const int brow = wn * T::TN + (lane & 31);
-    const int half = lane >> 5;
-    constexpr int KK = T::BK / 16;
-    constexpr int NM = T::FM * T::FN * NPASS;            // MFMAs per k-step
-    constexpr int NL = (T::IPW + KK - 1) / KK;           // loads per k-step
-    constexpr int EVERY = NM / NL > 0 ? NM / NL : 1;     // MFMAs between two loads
-    using Frag = typename T::Frag;
-    Frag fa0[2][T::FM], fb0[2][T::FN], fa1[2][T::FM], fb1[2][T::FN];
-    int q = 0;   // next load of slice kn (compile-time after unrolling)
+struct Frags {
+    typename T::Frag a0[T::FM], b0[T::FN], a1[T::FM], b1[T::FN];
+    __device__ __forceinline__ void read(const unsigned char* st, int kk, int wm, int wn, int lane) {
+        const unsigned char* sa0 = st;
+        const unsigned char* sa1 = st + T::A_BYTES;
+        const unsigned char* sb0 = st + T::NA * T::A_BYTES;
+        const unsigned char* sb1 = sb0 + T::B_BYTES;
+        const int arow = wm * T::TM + (lane & 31);
+        const int brow = wn * T::TN + (lane & 31);
+        const int c = 2 * kk + (lane >> 5);   // logical 16-byte chunk of the K-major rows
 #pragma unroll
-    for (int kk = 0; kk <= KK; ++kk) {
-        if (kk < KK) {
-            const int c = 2 * kk + half;   // logical 16-byte chunk of the K-major rows
-            const int slot = kk & 1;
+        for (int i = 0; i < T::FM; ++i)
+            a0[i] = *reinterpret_cast<const typename T::Frag*>(sa0 + kmajor_off<T>(arow + i * 32, c));
+#pragma unroll
+        for (int j = 0; j < T::FN; ++j) {
+            if constexpr (T::BT) b0[j] = b_frag_tr<T>(sb0, kk * 16, wn * T::TN + j * 32, lane);
+            else b0[j] = *reinterpret_cast<const typename T::Frag*>(sb0 + kmajor_off<T>(brow + j * 32, c));
+        }
+        if constexpr (NPASS >= 2) {
 #pragma unroll
             for (int i = 0; i < T::FM; ++i)
-                fa0[slot][i] = *reinterpret_cast<const Frag*>(sa0 + kmajor_off<T>(arow + i * 32, c));
+                a1[i] = *reinterpret_cast<const typename T::Frag*>(sa1 + kmajor_off<T>(arow + i * 32, c));
+        }
+        if constexpr (NPASS == 3) {
 #pragma unroll
             for (int j = 0; j < T::FN; ++j) {
-                if constexpr (T::BT) {
-                    fb0[slot][j] = b_frag_tr<T>(sb0, kk * 16, wn * T::TN + j * 32, lane);
-                } else {
-                    fb0[slot][j] = *reinterpret_cast<const Frag*>(sb0 + kmajor_off<T>(brow + j * 32, c));
-                }
+                if constexpr (T::BT) b1[j] = b_frag_tr<T>(sb1, kk * 16, wn * T::TN + j * 32, lane);
+                else b1[j] = *reinterpret_cast<const typename T::Frag*>(sb1 + kmajor_off<T>(brow + j * 32, c));
             }
-            if constexpr (NPASS >= 2) {
-#pragma unroll
-                for (int i = 0; i < T::FM; ++i)
-                    fa1[slot][i] = *reinterpret_cast<const Frag*>(sa1 + kmajor_off<T>(arow + i * 32, c));
-            }
-            if constexpr (NPASS == 3) {
-#pragma unroll
-                for (int j = 0; j < T::FN; ++j) {
-                    if constexpr (T::BT) {
-                        fb1[slot][j] = b_frag_tr<T>(sb1, kk * 16, wn * T::TN + j * 32, lane);
-                    } else {
-                        fb1[slot][j] = *reinterpret_cast<const Frag*>(sb1 + kmajor_off<T>(brow + j * 32, c));
-                    }
-                }
-            }
-        }
-        if (kk > 0) {
-            const int slot = (kk - 1) & 1;
-            int m = 0;
-#pragma unroll
-            for (int i = 0; i < T::FM; ++i)
-#pragma unroll
-                for (int j = 0; j < T::FN; ++j)
-#pragma unroll
-                    for (int p = 0; p < NPASS; ++p) {
-                        // per block: hi*lo, lo*hi, then hi*hi (the order of the sums)
-                        if (NPASS == 3 && p == 0) acc[i][j] = mfma32(fa0[slot][i], fb1[slot][j], acc[i][j]);
-                        else if (NPASS >= 2 && p == NPASS - 2) acc[i][j] = mfma32(fa1[slot][i], fb0[slot][j], acc[i][j]);
-                        else acc[i][j] = mfma32(fa0[slot][i], fb0[slot][j], acc[i][j]);
-                        if (++m % EVERY == 0 && q < T::IPW && q < kk * NL) {
-                            __builtin_amdgcn_sched_barrier(0);
-                            load_one<NPASS, T>(a, ldst, kn, abase, bbase, wave, lane, q);
-                            __builtin_amdgcn_sched_barrier(0);
-                            ++q;
-                        }
-                    }
         }
     }
+};
+
+// One k-step's MFMAs. With OVER > 0 the loads of a slice are spread over OVER
+// MFMAs, of which this step's are M0, M0 + 1, ...; each is fenced in place:
+// issued in one burst ahead of the MFMAs they hold the wave in the
+// vector-memory issue queue while its matrix pipe idles.
+template <int NPASS, typename T, int OVER, int M0>
+__device__ __forceinline__ void mma_step(f32x16 (&acc)[T::FM][T::FN], const Frags<NPASS, T>& f, const Loader<T>& ld,
+                                         unsigned char* dst, int wave) {
+    int m = M0;
 #pragma unroll
-    for (; q < T::IPW; ++q) load_one<NPASS, T>(a, ldst, kn, abase, bbase, wave, lane, q);
+    for (int i = 0; i < T::FM; ++i)
+#pragma unroll
+        for (int j = 0; j < T::FN; ++j)
+#pragma unroll
+            for (int p = 0; p < NPASS; ++p) {
+                // per block: hi*lo, lo*hi, then hi*hi (the order of the sums)
+                if (NPASS == 3 && p == 0) acc[i][j] = mfma32(f.a0[i], f.b1[j], acc[i][j]);
+                else if (NPASS >= 2 && p == NPASS - 2) acc[i][j] = mfma32(f.a1[i], f.b0[j], acc[i][j]);
+                else acc[i][j] = mfma32(f.a0[i], f.b0[j], acc[i][j]);
+                if constexpr (OVER > 0) {
+#pragma unroll
+                    for (int q = 0; q < T::IPW; ++q) {
+                        if (q * OVER / T::IPW == m) {
+                            __builtin_amdgcn_sched_barrier(0);
+                            ld.load(q, dst, wave);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    }
+                }
+                ++m;
+            }
 }
 
 // Store a wave's finished 32 x 32 block from its LDS tile (fp32, row pitch
@@ -350,7 +361,7 @@ __device__ __forceinline__ void store_block(const GemmArgs& a, int b, const floa
 }
 
 template <int NPASS, int EPI, typename T, bool SYM>
-__global__ __launch_bounds__(T::THREADS) void gemm(GemmArgs a) {
+__global__ __launch_bounds__(T::THREADS, T::MIN_WAVES) void gemm(GemmArgs a) {
     __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[T::SMEM];
 
     // XCD-aware tile order. Workgroups are dispatched round-robin over the
@@ -402,17 +413,11 @@ __global__ __launch_bounds__(T::THREADS) void gemm(GemmArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform per wave
     const int wm = wave / T::WN, wn = wave % T::WN;
 
-    const uint16_t* abase[2];
-    const uint16_t* bbase[2];
-    abase[0] = a.A0 + (int64_t)b * a.sA + (int64_t)row0 * a.lda;
-    abase[1] = NPASS >= 2 ? a.A1 + (int64_t)b * a.sA + (int64_t)row0 * a.lda : abase[0];
-    if constexpr (T::BT) {
-        bbase[0] = a.B0 + (int64_t)b * a.sB + col0;
-        bbase[1] = NPASS == 3 ? a.B1 + (int64_t)b * a.sB + col0 : bbase[0];
-    } else {
-        bbase[0] = a.B0 + (int64_t)b * a.sB + (int64_t)col0 * a.ldb;
-        bbase[1] = NPASS == 3 ? a.B1 + (int64_t)b * a.sB + (int64_t)col0 * a.ldb : bbase[0];
-    }
+    const uint16_t* abase0 = a.A0 + (int64_t)b * a.sA + (int64_t)row0 * a.lda;
+    const uint16_t* abase1 = NPASS >= 2 ? a.A1 + (int64_t)b * a.sA + (int64_t)row0 * a.lda : abase0;
+    const int64_t bo = (int64_t)b * a.sB + (T::BT ? (int64_t)col0 : (int64_t)col0 * a.ldb);
+    const uint16_t* bbase0 = a.B0 + bo;
+    const uint16_t* bbase1 = NPASS == 3 ? a.B1 + bo : bbase0;
 
     // Epilogue operands (Z for a Z, or A's hi / lo for the polynomial) are
     // fetched first so their latency hides behind the main loop.
@@ -470,34 +475,84 @@ __global__ __launch_bounds__(T::THREADS) void gemm(GemmArgs a) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-    // S-stage ring: slices 0..S-2 in flight before the first MFMA; at
-    // iteration kt slice kt+S-1 is requested into the stage freed by kt-1.
+    // S-stage ring. Plain loop: slices 0..S-2 in flight before the first MFMA;
+    // at iteration kt slice kt+S-1 is requested into the stage freed by kt-1.
+    // Run-on loop (PIPE): a slice's last k-step reads the next slice's first
+    // fragments, so the barrier between them stands among MFMAs already
+    // queued instead of ahead of idle ones; once a wave holds the last
+    // fragments of slice kt its stage is free, so S slices are in flight.
     // Requests past the last slice re-read it (in bounds) so every iteration
     // issues the same number of loads and the vmcnt wait stays exact.
+    // (16 x 8192 x 2048 at alpha 0.5: 3371 -> 3313 us a step.)
     int nk = a.K / T::BK;
     if constexpr (EPI == EPI_PART) {
         // this part's slices: the parts' lengths differ by at most one slice
         const int k0 = nk * part / a.ksplit;
         nk = nk * (part + 1) / a.ksplit - k0;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            abase[h] += (int64_t)k0 * T::BK;
-            bbase[h] += (int64_t)k0 * T::BK;
-        }
+        abase0 += (int64_t)k0 * T::BK;
+        abase1 += (int64_t)k0 * T::BK;
+        bbase0 += (int64_t)k0 * T::BK;
+        bbase1 += (int64_t)k0 * T::BK;
     }
+    Loader<T> ld;
+    ld.init(a, abase0, abase1, bbase0, bbase1, wave, lane);
+    constexpr int KK = T::BK / 16;
+    constexpr int NMFMA = T::FM * T::FN * NPASS;   // MFMAs per k-step
+    Frags<NPASS, T> f[2];
+    constexpr int AHEAD = T::PIPE ? T::S : T::S - 1;
 #pragma unroll
-    for (int p = 0; p < T::S - 1; ++p)
-        load_slice<NPASS, T>(a, smem_raw + p * T::STAGE_BYTES, p < nk ? p : nk - 1, abase, bbase, wave, lane);
-    for (int kt = 0; kt < nk; ++kt) {
-        // This wave's part of slice kt has landed; the bare barrier then makes
-        // every wave's part visible and frees stage kt-1 (its fragments were
-        // consumed by MFMAs issued before the barrier). A full __syncthreads
-        // would also drain the loads of the slices in flight behind kt.
-        wait_vmcnt<(T::S - 2) * T::IPW>();
+    for (int p = 0; p < AHEAD; ++p) {
+#pragma unroll
+        for (int q = 0; q < T::IPW; ++q) ld.load(q, smem_raw + p * T::STAGE_BYTES, wave);
+        if (p + 1 < nk) ld.advance(wave);
+    }
+    if constexpr (T::PIPE) {
+        wait_vmcnt<(T::S - 1) * T::IPW>();   // slice 0
         __builtin_amdgcn_s_barrier();
-        const int kn = kt + T::S - 1;
-        mma_slice<NPASS, T>(acc, smem_raw + (kt % T::S) * T::STAGE_BYTES, wm, wn, lane, a,
-                            smem_raw + (kn % T::S) * T::STAGE_BYTES, kn < nk ? kn : nk - 1, abase, bbase, wave);
+        asm volatile("" ::: "memory");
+        f[0].read(smem_raw, 0, wm, wn, lane);
+        for (int kt = 0; kt < nk; ++kt) {
+            unsigned char* st = smem_raw + (kt % T::S) * T::STAGE_BYTES;
+            const unsigned char* nx_st = smem_raw + ((kt + 1) % T::S) * T::STAGE_BYTES;
+#pragma unroll
+            for (int kk = 0; kk < KK - 1; ++kk) {
+                f[(kk + 1) & 1].read(st, kk + 1, wm, wn, lane);
+                mma_step<NPASS, T, 0, 0>(acc, f[kk & 1], ld, st, wave);
+            }
+            // slice kt's last fragments are in registers and this wave's part of
+            // slice kt+1 has landed; behind the barrier that holds for all waves
+            __builtin_amdgcn_sched_barrier(0);
+            wait_all_lds_vmcnt<(T::S - 2) * T::IPW>();
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            f[0].read(nx_st, 0, wm, wn, lane);
+            mma_step<NPASS, T, NMFMA, 0>(acc, f[(KK - 1) & 1], ld, st, wave);
+            if (kt + T::S + 1 < nk) ld.advance(wave);
+        }
+    } else {
+        for (int kt = 0; kt < nk; ++kt) {
+            // This wave's part of slice kt has landed; the bare barrier then makes
+            // every wave's part visible and frees stage kt-1 (its fragments were
+            // consumed by MFMAs issued before the barrier). A full __syncthreads
+            // would also drain the loads of the slices in flight behind kt.
+            wait_vmcnt<(T::S - 2) * T::IPW>();
+            __builtin_amdgcn_s_barrier();
+            const unsigned char* st = smem_raw + (kt % T::S) * T::STAGE_BYTES;
+            unsigned char* ldst = smem_raw + ((kt + T::S - 1) % T::S) * T::STAGE_BYTES;
+            f[0].read(st, 0, wm, wn, lane);
+            static_assert(KK == 2 || KK == 4, "two or four k-steps a slice");
+            f[1].read(st, 1, wm, wn, lane);
+            mma_step<NPASS, T, NMFMA * KK, 0>(acc, f[0], ld, ldst, wave);
+            if constexpr (KK == 4) {
+                f[0].read(st, 2, wm, wn, lane);
+                mma_step<NPASS, T, NMFMA * KK, NMFMA>(acc, f[1], ld, ldst, wave);
+                f[1].read(st, 3, wm, wn, lane);
+                mma_step<NPASS, T, NMFMA * KK, 2 * NMFMA>(acc, f[0], ld, ldst, wave);
+            }
+            mma_step<NPASS, T, NMFMA * KK, (KK - 1) * NMFMA>(acc, f[1], ld, ldst, wave);
+            if (kt + T::S < nk) ld.advance(wave);
+        }
     }
     wait_vmcnt<0>();   // no load may land in the ring once the epilogue reuses it
     __syncthreads();
@@ -1079,13 +1134,13 @@ SymPlan plan_sym(const GemmArgs& a, GemmEpi epi, int npass) {
 bool is_sym(GemmEpi epi) { return epi != EPI_UPDATE && epi != EPI_FINAL && epi != EPI_APPLY; }
 
 // A symmetric product on tile T, whole or split over K.
-template <int NPASS, int EPI, typename T>
+template <int NPASS, int EPI, typename T, bool SPLIT = false>
 hipError_t launch_sym(const GemmArgs& a0, int ksplit, hipStream_t s) {
     GemmArgs a = a0;
     if (T::BM == 64 && a.mreal) a.M = a.N = a.mreal;
     a.K = (a.K + T::BK - 1) / T::BK * T::BK;   // operands are zero to the next 128
     a.ksplit = ksplit;
-    if constexpr ((EPI == EPI_SPLIT || EPI == EPI_H16) && !T::F16) {
+    if constexpr (SPLIT && (EPI == EPI_SPLIT || EPI == EPI_H16)) {
         if (ksplit > 1) return launch_split<NPASS, EPI, T>(a, s);
     }
     return ksplit > 1 ? hipErrorInvalidValue : launch_tile<NPASS, EPI, T, true>(a, s);
@@ -1099,9 +1154,9 @@ hipError_t launch_sym(const GemmArgs& a0, int ksplit, hipStream_t s) {
 template <int EPI>
 hipError_t sym_one(const GemmArgs& a, const SymPlan& p, hipStream_t s) {
     switch (p.tile) {
-        case SYM_64: return launch_sym<1, EPI, Tile<1, 0, 64, 64, 64, 2, 2, 4>>(a, p.ksplit, s);
+        case SYM_64: return launch_sym<1, EPI, Tile<1, 0, 64, 64, 64, 2, 2, 4>, true>(a, p.ksplit, s);
         case SYM_256: return launch_sym<1, EPI, Tile<1, 0, 256, 256, kSliceK, 4, 2, 3>>(a, 1, s);
-        default: return launch_sym<1, EPI, Tile<1, 0, 128, 128, kSliceK, 2, 2, 4>>(a, p.ksplit, s);
+        default: return launch_sym<1, EPI, Tile<1, 0, 128, 128, kSliceK, 2, 2, 4>, true>(a, p.ksplit, s);
     }
 }
 template <int EPI>
@@ -1115,12 +1170,17 @@ hipError_t sym_f16(const GemmArgs& a, const SymPlan& p, hipStream_t s) {
 template <int EPI>
 hipError_t sym_three(const GemmArgs& a, const SymPlan& p, hipStream_t s) {
     switch (p.tile) {
-        case SYM_64: return launch_sym<3, EPI, Tile<3, 0, 64, 64, kSliceK, 2, 2, 4>>(a, p.ksplit, s);
+        case SYM_64: return launch_sym<3, EPI, Tile<3, 0, 64, 64, kSliceK, 2, 2, 4>, true>(a, p.ksplit, s);
         case SYM_64S2: return launch_sym<3, EPI, Tile<3, 0, 64, 64, kSliceK, 2, 2, 2>>(a, 1, s);
         case SYM_256:
             if constexpr (EPI == EPI_SPLIT) return launch_sym<3, EPI, Tile<3, 0, 256, 256, kSliceK, 2, 4, 2>>(a, 1, s);
             return hipErrorInvalidValue;
-        default: return launch_sym<3, EPI, Tile<3, 0, 128, 128, kSliceK, 4, 2, 2>>(a, 1, s);
+        default:
+            // from K = 1024 the slices pay for the run-on loop's longer start
+            // (s = 1024, 16 matrices: 72.3 against 74.7 us; s = 384, 64: 24.8
+            // against 23.1)
+            if (a.K >= 1024) return launch_sym<3, EPI, Tile<3, 0, 128, 128, kSliceK, 4, 2, 2, false, true>>(a, 1, s);
+            return launch_sym<3, EPI, Tile<3, 0, 128, 128, kSliceK, 4, 2, 2>>(a, 1, s);
     }
 }
 
