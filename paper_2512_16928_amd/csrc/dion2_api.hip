@@ -516,9 +516,10 @@ GemmArgs right_args(const Plan& P, const uint16_t* xh, const uint16_t* xl, const
 // The final Newton-Schulz product either stores O for the apply pass, in the
 // layout that pass reads along W's rows (L [kpad][opad] for row selection,
 // L^T [opad][kpad] for columns), or, for row selection with O in the L
-// layout and bf16 W, applies the update step itself (EPI_APPLY).
+// layout, applies the update step itself (EPI_APPLY, EPI_APPLY_F32).
 struct FinalSpec {
     bool fuse;          // EPI_APPLY instead of EPI_FINAL + K5
+    bool w_f32;
     MatSet ms;
     const int32_t* sel;
     double lr_eff;
@@ -537,7 +538,7 @@ GemmEpi final_output(const Plan& P, GemmArgs& x, float* O, const FinalSpec& f) {
         x.cols = P.cols;
         x.lr_eff = f.lr_eff;
         x.dbg = f.dbg;
-        return EPI_APPLY;
+        return f.w_f32 ? EPI_APPLY_F32 : EPI_APPLY;
     }
     x.out0 = O;
     x.sOut0 = P.kpad * P.opad;
@@ -1054,13 +1055,14 @@ int front(const Plan& P, const MatSet& ms, const Bufs& b, float mu, int ns_steps
 }
 
 // Whether the final Newton-Schulz product applies the update itself (row
-// selection with O in the L layout and bf16 W), and its operands.
+// selection with O in the L layout, rows of at least the 16 entries a lane
+// updates at once), and its operands.
 FinalSpec make_final(const Plan& P, const MatSet& ms, const Bufs& b, float lr, int ns_steps,
                      const dion2_options& opt) {
     FinalSpec fin{};
     fin.lr_eff = (double)lr * std::sqrt((double)P.rows / (double)P.cols);
-    fin.fuse = ns_steps > 0 && P.axis == 0 && P.z_is_L && opt.w_dtype == DION2_DTYPE_BF16 &&
-               P.cols % 8 == 0 && P.cols >= 16;
+    fin.fuse = ns_steps > 0 && P.axis == 0 && P.z_is_L && P.cols >= 16;
+    fin.w_f32 = opt.w_dtype == DION2_DTYPE_F32;
     fin.ms = ms;
     fin.sel = b.sel;
     fin.dbg = opt.dbg_update;

@@ -47,13 +47,16 @@ struct MatSet {
 // ------------------------------------------------------- global accesses
 // Pointers reached through MatSet (possibly from a device pointer table) are
 // generic; these helpers access them as global memory, so the compiler emits
-// global (not flat) loads and stores and waits on vmcnt alone.
+// global (not flat) loads and stores and waits on vmcnt alone. Vectors need
+// only their elements' alignment (two bytes for bf16): with amdhsa's
+// unaligned access mode one instruction fetches them from any address, so
+// rows of any length take the vector paths.
 #define DION2_GLOBAL __attribute__((address_space(1)))
 template <int N> struct RawBits;
 template <> struct RawBits<2> { typedef unsigned short T; };
 template <> struct RawBits<4> { typedef unsigned int T; };
-template <> struct RawBits<8> { typedef unsigned int T __attribute__((ext_vector_type(2))); };
-template <> struct RawBits<16> { typedef unsigned int T __attribute__((ext_vector_type(4))); };
+template <> struct RawBits<8> { typedef unsigned int T __attribute__((ext_vector_type(2), aligned(2))); };
+template <> struct RawBits<16> { typedef unsigned int T __attribute__((ext_vector_type(4), aligned(2))); };
 template <typename V>
 __device__ __forceinline__ V ldg(const void* p) {
     typedef typename RawBits<sizeof(V)>::T R;
@@ -132,7 +135,50 @@ template <> struct Elem<uint16_t> {
     static __device__ __forceinline__ void lds_store_f64(uint16_t* p, double v) { *p = f64_to_bf16(v); }
 };
 
-// four consecutive elements as fp32 (p is 8-byte aligned for bf16, 16 for fp32)
+// Four consecutive elements of a row as they are stored, of which the first n
+// exist (the others read as zero); n >= 4 is one vector access. Without
+// RAGGED n is at least 4 or at most 0 (the row's length is a multiple of 4):
+// no code or registers for parts of a quad.
+template <typename T> struct Quad;
+template <> struct Quad<float> { typedef float4 V; };
+template <> struct Quad<uint16_t> { typedef uint2 V; };
+__device__ __forceinline__ float4 load_part(const float* p, int64_t n) {
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (n > 0) v.x = ldg<float>(p);
+    if (n > 1) v.y = ldg<float>(p + 1);
+    if (n > 2) v.z = ldg<float>(p + 2);
+    return v;
+}
+__device__ __forceinline__ uint2 load_part(const uint16_t* p, int64_t n) {
+    uint2 v = make_uint2(0u, 0u);
+    if (n > 0) v.x = ldg<uint16_t>(p);
+    if (n > 1) v.x |= (uint32_t)ldg<uint16_t>(p + 1) << 16;
+    if (n > 2) v.y = ldg<uint16_t>(p + 2);
+    return v;
+}
+__device__ __forceinline__ void store_part(float* p, const float4& v, int64_t n) {
+    if (n > 0) stg(p, v.x);
+    if (n > 1) stg(p + 1, v.y);
+    if (n > 2) stg(p + 2, v.z);
+}
+__device__ __forceinline__ void store_part(uint16_t* p, const uint2& v, int64_t n) {
+    if (n > 0) stg(p, (uint16_t)v.x);
+    if (n > 1) stg(p + 1, (uint16_t)(v.x >> 16));
+    if (n > 2) stg(p + 2, (uint16_t)v.y);
+}
+template <bool RAGGED = true, typename T>
+__device__ __forceinline__ typename Quad<T>::V load_quad(const T* p, int64_t n) {
+    if (n >= 4) return ldg_nt<typename Quad<T>::V>(p);
+    if constexpr (RAGGED) return load_part(p, n);
+    return typename Quad<T>::V{};
+}
+template <bool RAGGED = true, typename T>
+__device__ __forceinline__ void store_quad(T* p, const typename Quad<T>::V& v, int64_t n) {
+    if (n >= 4) stg_nt(p, v);
+    else if constexpr (RAGGED) store_part(p, v, n);
+}
+
+// four consecutive elements as fp32
 __device__ __forceinline__ void load4(const float* p, float (&v)[4]) {
     const float4 x = ldg<float4>(p);
     v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
@@ -272,7 +318,8 @@ hipError_t launch_copy_compact(const CompactCopyArgs& a, hipStream_t s);
 //              O = ca E0 + C (row selection, O in the L layout) is not
 //              stored; the update step is applied directly:
 //              W[K[p]][j] <- bf16(W[K[p]][j] - lr_eff O[p][j]) for p < k,
-//              j < d_oth (bf16 W, cols % 8 == 0); dbg gets O if set
+//              j < d_oth (bf16 W, cols >= 16); dbg gets O if set
+//   EPI_APPLY_F32  the same with fp32 W
 //   EPI_H16    (B as rows [N][K], symmetric C; npass 1): out0 = fp16(2^oexp C)
 //   EPI_QPOLY_H16 (B as rows [N][K], npass 1, fp16 operands and E0):
 //              Q = ca I + cb 2^eexp E0 + cc 2^oexp C, out0 = fp16(2^sexp Q)
@@ -287,7 +334,7 @@ hipError_t launch_copy_compact(const CompactCopyArgs& a, hipStream_t s);
 //   EPI_PART   a symmetric product's partial sums over one part of K, left in
 //              `part` for a second launch (internal to launch_gemm)
 enum GemmEpi { EPI_SPLIT = 0, EPI_POLY = 1, EPI_UPDATE = 2, EPI_FINAL = 3, EPI_QPOLY = 4,
-               EPI_APPLY = 5, EPI_H16 = 6, EPI_QPOLY_H16 = 7, EPI_POLY_H16 = 8, EPI_PART = 9 };
+               EPI_APPLY = 5, EPI_H16 = 6, EPI_QPOLY_H16 = 7, EPI_POLY_H16 = 8, EPI_PART = 9, EPI_APPLY_F32 = 10 };
 struct GemmArgs {
     const uint16_t* A0; const uint16_t* A1;   // A operand(s), [M][K] ld lda
     const uint16_t* B0; const uint16_t* B1;   // B operand(s), [N][K] or [K][N], ld ldb
@@ -323,7 +370,7 @@ struct GemmArgs {
     float* part;
     int64_t part_floats;
     int ksplit;
-    // EPI_APPLY only
+    // EPI_APPLY, EPI_APPLY_F32 only
     MatSet ms;                                 // W
     const int32_t* sel;                        // [batch][k]
     int k, d_oth;

@@ -9,14 +9,13 @@
 //
 // Row mode reads O rows and W rows along j (both contiguous). Column mode
 // streams W by rows and reads O transposed, in one of three kernels:
-//   apply_cols_sel    column count a multiple of 8 and a row of W within
-//                     8 KB (the common case): one row per wave, copied into
-//                     LDS, one fp64 update per selected entry per lane;
-//   apply_cols_strip  wider rows: 512-column strips, the strip's slice of
-//                     O^T staged in LDS, only chunks with a selected column
-//                     rewritten;
-//   apply_cols        other column counts: four (or one) columns per lane.
-#include <type_traits>
+//   apply_cols_sel    a row of W within 8 KB (the common case): one row per
+//                     wave, copied into LDS, one fp64 update per selected
+//                     entry per lane;
+//   apply_cols_strip  wider rows, column count a multiple of 8: 512-column
+//                     strips, the strip's slice of O^T staged in LDS, only
+//                     chunks with a selected column rewritten;
+//   apply_cols        other column counts: four columns per lane.
 
 #include "dion2_device.h"
 
@@ -25,28 +24,27 @@ namespace {
 
 constexpr int kThreads = 256;
 
+// four stored entries minus lr_eff times four of O, each rounded once
+__device__ __forceinline__ float4 update4(const float4& w, const float (&o)[4], double lr_eff) {
+    float x[4];
+    unpack4(w, x);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) x[v] = (float)__dsub_rn((double)x[v], __dmul_rn(lr_eff, (double)o[v]));
+    return make_float4(x[0], x[1], x[2], x[3]);
+}
+__device__ __forceinline__ uint2 update4(const uint2& w, const float (&o)[4], double lr_eff) {
+    float x[4];
+    unpack4(w, x);
+    uint32_t h[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) h[v] = f64_to_bf16(__dsub_rn((double)x[v], __dmul_rn(lr_eff, (double)o[v])));
+    return make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+}
+
+// Row mode, where the final product does not apply the update itself (O of
+// the other orientation, or no Newton-Schulz step): one wave per selected
+// line p, four entries per lane, four quads in flight.
 template <typename WT>
-__device__ __forceinline__ void update(WT* w, float o, double lr_eff) {
-    const double x = (double)Elem<WT>::load(w);
-    const double r = __dsub_rn(x, __dmul_rn(lr_eff, (double)o));
-    Elem<WT>::store_f64(w, r);
-}
-
-// four consecutive elements of W: load as fp32, store rounded from fp64
-__device__ __forceinline__ void load4w(const float* p, float (&v)[4]) { load4(p, v); }
-__device__ __forceinline__ void load4w(const uint16_t* p, float (&v)[4]) { load4(p, v); }
-__device__ __forceinline__ void store4w(float* p, const double (&r)[4]) {
-    stg(p, make_float4((float)r[0], (float)r[1], (float)r[2], (float)r[3]));
-}
-__device__ __forceinline__ void store4w(uint16_t* p, const double (&r)[4]) {
-    uint2 u;
-    u.x = (uint32_t)f64_to_bf16(r[0]) | ((uint32_t)f64_to_bf16(r[1]) << 16);
-    u.y = (uint32_t)f64_to_bf16(r[2]) | ((uint32_t)f64_to_bf16(r[3]) << 16);
-    stg(p, u);
-}
-
-// Row mode: one wave per selected line p, four elements per lane.
-template <int VEC, typename WT>
 __global__ __launch_bounds__(kThreads) void apply_rows(ApplyArgs a) {
     const int b = blockIdx.y;
     const int lane = threadIdx.x & 63;
@@ -55,21 +53,23 @@ __global__ __launch_bounds__(kThreads) void apply_rows(ApplyArgs a) {
     WT* __restrict__ w = a.ms.w<WT>(b) + (int64_t)a.sel[(int64_t)b * a.k + p] * a.cols;
     const float* __restrict__ o = a.O + (int64_t)b * a.kpad * a.opad + (int64_t)p * a.opad;
     float* dbg = a.dbg ? a.dbg + ((int64_t)b * a.k + p) * a.d_oth : nullptr;
-    if constexpr (VEC == 4) {
-        for (int j = 4 * lane; j < a.d_oth; j += 256) {
-            float x[4], u[4];
-            load4w(w + j, x);
-            load4(o + j, u);
-            double r[4];
+    constexpr int kQ = 4;
+    for (int j0 = 4 * lane; j0 - 4 * lane < a.d_oth; j0 += 256 * kQ) {
+        typename Quad<WT>::V x[kQ];
+        float4 u[kQ];
 #pragma unroll
-            for (int v = 0; v < 4; ++v) r[v] = __dsub_rn((double)x[v], __dmul_rn(a.lr_eff, (double)u[v]));
-            store4w(w + j, r);
-            if (dbg) *reinterpret_cast<float4*>(dbg + j) = make_float4(u[0], u[1], u[2], u[3]);
+        for (int q = 0; q < kQ; ++q) {
+            const int j = j0 + 256 * q;
+            x[q] = load_quad(w + j, a.d_oth - j);
+            u[q] = load_quad(o + j, a.d_oth - j);
         }
-    } else {
-        for (int j = lane; j < a.d_oth; j += 64) {
-            update(w + j, o[j], a.lr_eff);
-            if (dbg) dbg[j] = o[j];
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) {
+            const int j = j0 + 256 * q;
+            float uv[4];
+            unpack4(u[q], uv);
+            store_quad(w + j, update4(x[q], uv, a.lr_eff), a.d_oth - j);
+            if (dbg) store_quad(dbg + j, u[q], a.d_oth - j);
         }
     }
 }
@@ -84,7 +84,7 @@ __global__ __launch_bounds__(kThreads) void apply_rows(ApplyArgs a) {
 constexpr int kCW = 256;
 constexpr int kRB = 64;
 
-template <int VEC, typename WT>
+template <typename WT>
 __global__ __launch_bounds__(kThreads) void apply_cols(ApplyArgs a) {
     const int b = blockIdx.z;
     const int64_t c0 = (int64_t)blockIdx.x * kCW;
@@ -103,15 +103,15 @@ __global__ __launch_bounds__(kThreads) void apply_cols(ApplyArgs a) {
         for (int v = 0; v < 4; ++v) p[v] = (c + v < a.cols && rk[v + 1] > rk[v]) ? rk[v] : -1;
     }
     constexpr int kR = kRB / 4;   // rows per thread
-    if (VEC == 4 && c + 3 < a.cols) {
-        typedef typename std::conditional<sizeof(WT) == 2, uint2, float4>::type Raw;
-        Raw raw[kR];
+    {
+        const int64_t n = a.cols - c;   // columns of this lane that exist
+        typename Quad<WT>::V raw[kR];
         float o[kR][4];
-        // branch-free loads so all of them are in flight together: an
+        // branch-free loads of O so all of them are in flight together: an
         // unselected column reads the block's first line (a word of the same
-        // row segment, so no extra cache line; unused), rows past the matrix
-        // read its last row
-        const int pfirst = ldg<int32_t>(rank + c0);
+        // row segment, so no extra cache line; unused; the last line where the
+        // block has none), rows past the matrix read its last row
+        const int pfirst = min(ldg<int32_t>(rank + c0), a.k - 1);
         int pc[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) pc[v] = p[v] >= 0 ? p[v] : pfirst;
@@ -119,7 +119,7 @@ __global__ __launch_bounds__(kThreads) void apply_cols(ApplyArgs a) {
         for (int i = 0; i < kR; ++i) {
             int64_t r = r0 + rg + 4 * i;
             r = r < a.rows ? r : a.rows - 1;
-            raw[i] = ldg_nt<Raw>(W + r * a.cols + c);
+            raw[i] = load_quad(W + r * a.cols + c, n);
 #pragma unroll
             for (int v = 0; v < 4; ++v) o[i][v] = OT[r * a.kpad + pc[v]];
         }
@@ -129,30 +129,22 @@ __global__ __launch_bounds__(kThreads) void apply_cols(ApplyArgs a) {
             if (r >= a.rows) continue;
             // unselected entries are written back with their own bits
             if constexpr (sizeof(WT) == 2) {
-                const uint2 x = reinterpret_cast<const uint2&>(raw[i]);
+                const uint2 x = raw[i];
                 uint32_t h[4] = {x.x & 0xffffu, x.x >> 16, x.y & 0xffffu, x.y >> 16};
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
                     if (p[v] >= 0)
                         h[v] = f64_to_bf16(__dsub_rn((double)bf16_bits_to_f32(h[v]),
                                                      __dmul_rn(a.lr_eff, (double)o[i][v])));
-                stg_nt(W + r * a.cols + c, make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16)));
+                store_quad(W + r * a.cols + c, make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16)), n);
             } else {
-                float4 x = reinterpret_cast<const float4&>(raw[i]);
-                float f[4] = {x.x, x.y, x.z, x.w};
+                float f[4];
+                unpack4(raw[i], f);
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
                     if (p[v] >= 0) f[v] = (float)__dsub_rn((double)f[v], __dmul_rn(a.lr_eff, (double)o[i][v]));
-                stg_nt(W + r * a.cols + c, make_float4(f[0], f[1], f[2], f[3]));
+                store_quad(W + r * a.cols + c, make_float4(f[0], f[1], f[2], f[3]), n);
             }
-        }
-    } else {
-        for (int rl = rg; rl < kRB; rl += 4) {
-            const int64_t r = r0 + rl;
-            if (r >= a.rows) break;
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                if (p[v] >= 0) update(W + r * a.cols + c + v, OT[r * a.kpad + p[v]], a.lr_eff);
         }
     }
     if (a.dbg) {   // O in the [k][d_oth] layout (inspection only)
@@ -188,6 +180,15 @@ struct Chunk8<uint16_t> {
     uint4 u;
     __device__ __forceinline__ void load(const uint16_t* p) { u = ldg_nt<uint4>(p); }
     __device__ __forceinline__ void store(uint16_t* p) const { stg_nt(p, u); }
+    // the first n entries (n >= 8: all of them)
+    __device__ __forceinline__ void load_part(const uint16_t* p, int n) {
+        const uint2 a = load_quad(p, n), b = load_quad(p + 4, n - 4);
+        u = make_uint4(a.x, a.y, b.x, b.y);
+    }
+    __device__ __forceinline__ void store_part(uint16_t* p, int n) const {
+        store_quad(p, make_uint2(u.x, u.y), n);
+        store_quad(p + 4, make_uint2(u.z, u.w), n - 4);
+    }
     __device__ __forceinline__ void put(uint16_t* lds) const { *reinterpret_cast<uint4*>(lds) = u; }
     __device__ __forceinline__ void get_lds(const uint16_t* lds) { u = *reinterpret_cast<const uint4*>(lds); }
     __device__ __forceinline__ float get(int v) const {
@@ -210,6 +211,14 @@ struct Chunk8<float> {
     __device__ __forceinline__ void store(float* p) const {
         stg_nt(p, make_float4(f[0], f[1], f[2], f[3]));
         stg_nt(p + 4, make_float4(f[4], f[5], f[6], f[7]));
+    }
+    __device__ __forceinline__ void load_part(const float* p, int n) {
+        unpack4(load_quad(p, n), *reinterpret_cast<float(*)[4]>(&f[0]));
+        unpack4(load_quad(p + 4, n - 4), *reinterpret_cast<float(*)[4]>(&f[4]));
+    }
+    __device__ __forceinline__ void store_part(float* p, int n) const {
+        store_quad(p, make_float4(f[0], f[1], f[2], f[3]), n);
+        store_quad(p + 4, make_float4(f[4], f[5], f[6], f[7]), n - 4);
     }
     __device__ __forceinline__ void put(float* lds) const {
         reinterpret_cast<float4*>(lds)[0] = make_float4(f[0], f[1], f[2], f[3]);
@@ -294,13 +303,13 @@ __global__ __launch_bounds__(kThreads) void apply_cols_strip(ApplyArgs a) {
     }
 }
 
-// Column mode, cols % 8 == 0 and a row of W within 8 KB: whole
-// rows per wave, the arithmetic spread over the selected entries rather
+// Column mode, a row of W within 8 KB: whole rows per wave, the arithmetic spread over the selected entries rather
 // than over the columns. A wave copies its row of W into LDS (16-byte
 // chunks), lane l updates there the entries of ranks p = l + 64 t (column
 // K[p], value O^T[r][p], read coalesced), and the row goes back to W whole.
 // Every lane does the same number of updates, so nothing diverges; K is
-// staged in LDS once per block. The first 64 KT ranks of a row are fetched
+// staged in LDS once per block. A row whose length is not a multiple of 8
+// (`ragged`) ends in part of a chunk. The first 64 KT ranks of a row are fetched
 // with the row (one row ahead); larger k take further passes of 64 KT.
 constexpr int kSelRows = 32;                 // rows per block (8 per wave)
 constexpr int kSelRowBytes = 8192;           // LDS row buffer per wave
@@ -341,14 +350,21 @@ __global__ __launch_bounds__(kThreads) void apply_cols_sel(ApplyArgs a) {
         cval[j] = c < a.cols;
         coff[j] = cval[j] ? c : (int)a.cols - kLaneCols;
     }
+    const bool ragged = a.cols % kLaneCols != 0;   // uniform
+    auto left = [&](int j) { return (int)a.cols - kLaneCols * (lane + 64 * j); };   // columns from a chunk's first
     // Software pipelined over the wave's rows: the loads of the next row are
     // issued before the stores of this one. Vector memory counters retire in
     // issue order, so a wait for loads issued after a row's stores would also
     // wait for those stores to be acknowledged; issued before them, it does
     // not. The last row's "next" loads re-read that row, unused.
     auto load_row = [&](int64_t r, Chunk8<WT> (&w)[NCH], float (&o)[KT]) {
+        if (!ragged) {
 #pragma unroll
-        for (int j = 0; j < NCH; ++j) w[j].load(W + r * a.cols + coff[j]);
+            for (int j = 0; j < NCH; ++j) w[j].load(W + r * a.cols + coff[j]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < NCH; ++j) w[j].load_part(W + r * a.cols + kLaneCols * (lane + 64 * j), left(j));
+        }
         const float* src = OT + r * a.kpad;
 #pragma unroll
         for (int t = 0; t < KT; ++t) {
@@ -395,7 +411,8 @@ __global__ __launch_bounds__(kThreads) void apply_cols_sel(ApplyArgs a) {
         for (int j = 0; j < NCH; ++j) {
             if (cval[j]) {
                 w[j].get_lds(rs + coff[j]);
-                w[j].store(W + r * a.cols + coff[j]);
+                if (!ragged) w[j].store(W + r * a.cols + coff[j]);
+                else w[j].store_part(W + r * a.cols + coff[j], left(j));
             }
         }
         __builtin_amdgcn_wave_barrier();   // the row buffer is rewritten next
@@ -418,7 +435,7 @@ void launch_cols_sel_k(const ApplyArgs& a, hipStream_t s) {
 template <typename WT>
 bool launch_cols_sel(const ApplyArgs& a, hipStream_t s) {
     constexpr int64_t kMaxCols = kSelRowBytes / sizeof(WT);
-    if (a.cols % kLaneCols || a.cols > kMaxCols || a.k > kSelMaxK) return false;
+    if (a.cols < kLaneCols || a.cols > kMaxCols || a.k > kSelMaxK) return false;
     const int64_t nch = (a.cols + kStrip - 1) / kStrip;
     if (nch <= 1) launch_cols_sel_k<WT, 1>(a, s);
     else if (nch <= 2) launch_cols_sel_k<WT, 2>(a, s);
@@ -431,16 +448,10 @@ bool launch_cols_sel(const ApplyArgs& a, hipStream_t s) {
 }  // namespace
 
 hipError_t launch_apply(const ApplyArgs& a, int axis, int w_bf16, hipStream_t s) {
-    const bool vec = a.cols % 4 == 0;
     if (axis == 0) {
         dim3 grid((unsigned)((a.k + 3) / 4), (unsigned)a.batch);
-        if (w_bf16) {
-            if (vec) hipLaunchKernelGGL((apply_rows<4, uint16_t>), grid, dim3(kThreads), 0, s, a);
-            else hipLaunchKernelGGL((apply_rows<1, uint16_t>), grid, dim3(kThreads), 0, s, a);
-        } else {
-            if (vec) hipLaunchKernelGGL((apply_rows<4, float>), grid, dim3(kThreads), 0, s, a);
-            else hipLaunchKernelGGL((apply_rows<1, float>), grid, dim3(kThreads), 0, s, a);
-        }
+        if (w_bf16) hipLaunchKernelGGL((apply_rows<uint16_t>), grid, dim3(kThreads), 0, s, a);
+        else hipLaunchKernelGGL((apply_rows<float>), grid, dim3(kThreads), 0, s, a);
     } else if (w_bf16 ? launch_cols_sel<uint16_t>(a, s) : launch_cols_sel<float>(a, s)) {
         // whole rows per wave, one update per selected entry
     } else if (a.cols % kLaneCols == 0) {
@@ -451,13 +462,8 @@ hipError_t launch_apply(const ApplyArgs& a, int axis, int w_bf16, hipStream_t s)
     } else {
         dim3 grid((unsigned)((a.cols + kCW - 1) / kCW), (unsigned)((a.rows + kRB - 1) / kRB),
                   (unsigned)a.batch);
-        if (w_bf16) {
-            if (vec) hipLaunchKernelGGL((apply_cols<4, uint16_t>), grid, dim3(kThreads), 0, s, a);
-            else hipLaunchKernelGGL((apply_cols<1, uint16_t>), grid, dim3(kThreads), 0, s, a);
-        } else {
-            if (vec) hipLaunchKernelGGL((apply_cols<4, float>), grid, dim3(kThreads), 0, s, a);
-            else hipLaunchKernelGGL((apply_cols<1, float>), grid, dim3(kThreads), 0, s, a);
-        }
+        if (w_bf16) hipLaunchKernelGGL((apply_cols<uint16_t>), grid, dim3(kThreads), 0, s, a);
+        else hipLaunchKernelGGL((apply_cols<float>), grid, dim3(kThreads), 0, s, a);
     }
     return hipGetLastError();
 }

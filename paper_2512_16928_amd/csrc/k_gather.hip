@@ -12,8 +12,6 @@
 // (line p, other index j): the side that is contiguous in M is read and
 // written directly, the other side goes through an LDS tile. Tiles cover the
 // padded extents, and padding (p >= k or j >= d_oth) is written as zero.
-#include <type_traits>
-
 #include "dion2_device.h"
 
 namespace dion2 {
@@ -37,7 +35,7 @@ __device__ __forceinline__ void pack_hilo4(const float (&x)[4], uint2* hi, uint2
 }
 
 // Row mode: line p is row K[p] of M; j runs along the row (contiguous).
-template <int VEC>
+template <bool RAGGED>
 __global__ __launch_bounds__(kThreads) void gather_rows(GatherArgs a) {
     __shared__ float tile[kT][kT + 1];
     const int b = blockIdx.z;
@@ -55,38 +53,27 @@ __global__ __launch_bounds__(kThreads) void gather_rows(GatherArgs a) {
     // store would also wait for the store's acknowledgement
     int64_t roff[4];
     float4 mv[4];
-    const bool vec = VEC == 4 && j + 3 < a.d_oth;
+    const int n = a.d_oth - j;   // entries of this lane's quads that exist
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int p = p0 + ty + 16 * i;
         roff[i] = (int64_t)ldg<int32_t>(K + (p < a.k ? p : a.k - 1)) * a.cols;
     }
-    if (vec) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) mv[i] = ldg_nt<float4>(M + roff[i] + j);
-    }
+    for (int i = 0; i < 4; ++i) mv[i] = load_quad<RAGGED>(M + roff[i] + j, n);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int pl = ty + 16 * i;
         const int p = p0 + pl;
         float x[4] = {0.f, 0.f, 0.f, 0.f};
         if (p < a.k) {
-            float* row = M + roff[i];
-            if (vec) {
-                float m[4];
-                unpack4(mv[i], m);
+            float m[4];
+            unpack4(mv[i], m);   // zeros past d_oth
 #pragma unroll
-                for (int v = 0; v < 4; ++v) x[v] = m[v] * sc;
-                if (a.decay) stg_nt(row + j, make_float4(a.mu * m[0], a.mu * m[1], a.mu * m[2], a.mu * m[3]));
-            } else {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    if (j + v < a.d_oth) {
-                        const float m = ldg<float>(row + j + v);
-                        x[v] = m * sc;
-                        if (a.decay) stg(row + j + v, a.mu * m);
-                    }
-                }
+            for (int v = 0; v < 4; ++v) x[v] = v < n ? m[v] * sc : 0.f;
+            if (a.decay) {
+                const float4 d = make_float4(a.mu * m[0], a.mu * m[1], a.mu * m[2], a.mu * m[3]);
+                store_quad<RAGGED>(M + roff[i] + j, d, n);
             }
         }
         if (L) {
@@ -128,7 +115,7 @@ __global__ __launch_bounds__(kThreads) void gather_rows(GatherArgs a) {
 constexpr int kCW = 256;
 constexpr int kRB = 64;
 
-template <int VEC, typename GT>
+template <typename GT, bool RAGGED>
 __global__ __launch_bounds__(kThreads) void update_cols(GatherArgs a) {
     __shared__ float tile[kCW][kRB + 1];   // [p - p0][r - r0]
     const int b = blockIdx.z;
@@ -145,29 +132,26 @@ __global__ __launch_bounds__(kThreads) void update_cols(GatherArgs a) {
     const int cq = threadIdx.x & 63, rg = threadIdx.x >> 6;
     const int64_t c = c0 + 4 * cq;
     int pl[4];        // tile row of each of the four columns, -1 if unselected
-    bool in[4];
     {
         int rk[5];   // rank[c .. c + 4], clamped to the array (branch-free loads)
 #pragma unroll
         for (int v = 0; v < 5; ++v) rk[v] = ldg<int32_t>(rank + (c + v < a.cols ? c + v : a.cols));
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            in[v] = c + v < a.cols;
-            pl[v] = (in[v] && rk[v + 1] > rk[v]) ? rk[v] - p0 : -1;
-        }
+        for (int v = 0; v < 4; ++v) pl[v] = (c + v < a.cols && rk[v + 1] > rk[v]) ? rk[v] - p0 : -1;
     }
     constexpr int kR = kRB / 4;   // rows per thread
-    if (VEC == 4 && in[3]) {
+    {
         // every row's M and G are loaded before the first store
-        typedef typename std::conditional<sizeof(GT) == 2, uint2, float4>::type GRaw;
+        typedef typename Quad<GT>::V GRaw;
+        const int64_t n = a.cols - c;   // columns of this lane that exist
         float4 mr[kR];
         GRaw gr[kR];
 #pragma unroll
         for (int i = 0; i < kR; ++i) {
             const int64_t r = r0 + rg + 4 * i;
             if (r < a.rows) {
-                mr[i] = ldg_nt<float4>(M + r * a.cols + c);
-                gr[i] = ldg_nt<GRaw>(G + r * a.cols + c);
+                mr[i] = load_quad<RAGGED>(M + r * a.cols + c, n);
+                gr[i] = load_quad<RAGGED>(G + r * a.cols + c, n);
             }
         }
 #pragma unroll
@@ -186,30 +170,11 @@ __global__ __launch_bounds__(kThreads) void update_cols(GatherArgs a) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
                     o[v] = (a.decay == 2 || (a.decay == 1 && pl[v] >= 0)) ? a.mu * m[v] : m[v];
-                stg_nt(M + r * a.cols + c, make_float4(o[0], o[1], o[2], o[3]));
+                store_quad<RAGGED>(M + r * a.cols + c, make_float4(o[0], o[1], o[2], o[3]), n);
             }
 #pragma unroll
             for (int v = 0; v < 4; ++v)
                 if (pl[v] >= 0) tile[pl[v]][rl] = m[v] * sc;   // rows past d_oth give zeros
-        }
-    } else {
-        for (int i = 0; i < kR; ++i) {
-            const int rl = rg + 4 * i;
-            const int64_t r = r0 + rl;
-            float m[4] = {0.f, 0.f, 0.f, 0.f};
-            if (r < a.rows) {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    if (in[v]) {
-                        m[v] = ldg<float>(M + r * a.cols + c + v) + Elem<GT>::load(G + r * a.cols + c + v);
-                        stg(M + r * a.cols + c + v,
-                            (a.decay == 2 || (a.decay == 1 && pl[v] >= 0)) ? a.mu * m[v] : m[v]);
-                    }
-                }
-            }
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                if (pl[v] >= 0) tile[pl[v]][rl] = m[v] * sc;
         }
     }
     __syncthreads();
@@ -431,21 +396,13 @@ hipError_t launch_colpass_finish(const ColpassArgs& a, hipStream_t s) {
 hipError_t launch_gather(const GatherArgs& a, int axis, int g_bf16, hipStream_t s) {
     if (axis == 0) {
         dim3 grid((unsigned)(a.opad / kT), (unsigned)(a.kpad / kT), (unsigned)a.batch);
-        if (a.cols % 4 == 0) {
-            hipLaunchKernelGGL((gather_rows<4>), grid, dim3(kThreads), 0, s, a);
-        } else {
-            hipLaunchKernelGGL((gather_rows<1>), grid, dim3(kThreads), 0, s, a);
-        }
+        if (a.cols % 4) hipLaunchKernelGGL(gather_rows<true>, grid, dim3(kThreads), 0, s, a);
+        else hipLaunchKernelGGL(gather_rows<false>, grid, dim3(kThreads), 0, s, a);
     } else {
         dim3 grid((unsigned)((a.cols + kCW - 1) / kCW), (unsigned)(a.opad / kRB), (unsigned)a.batch);
-        const bool vec = a.cols % 4 == 0;
-        if (g_bf16) {
-            if (vec) hipLaunchKernelGGL((update_cols<4, uint16_t>), grid, dim3(kThreads), 0, s, a);
-            else hipLaunchKernelGGL((update_cols<1, uint16_t>), grid, dim3(kThreads), 0, s, a);
-        } else {
-            if (vec) hipLaunchKernelGGL((update_cols<4, float>), grid, dim3(kThreads), 0, s, a);
-            else hipLaunchKernelGGL((update_cols<1, float>), grid, dim3(kThreads), 0, s, a);
-        }
+        auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, a); };
+        if (g_bf16) a.cols % 4 ? launch(update_cols<uint16_t, true>) : launch(update_cols<uint16_t, false>);
+        else a.cols % 4 ? launch(update_cols<float, true>) : launch(update_cols<float, false>);
     }
     return hipGetLastError();
 }

@@ -144,58 +144,58 @@ __device__ __forceinline__ int nmajor_off(int r, int c) {
 
 // This wave's part of the operands' K-slices. Wave w owns a stage's 1 KB
 // blocks w, w + WAVES, ...; lane i of a block fills the block's 16-byte slot
-// i with the global chunk that belongs there. The operand's address is
-// uniform and moves on by one slice at a time; a lane's offset from it is
-// fixed, so a load in the loop costs scalar work alone.
+// i with the global chunk that belongs there. A block is some rows of one
+// operand tile: its first row's address is uniform and moves on by one slice
+// at a time, and a lane's offset from it (row within the block, swizzled
+// chunk) is the same for all of a wave's blocks of an operand, so a load in
+// the loop costs scalar work alone and two registers hold the offsets.
 template <typename T>
 struct Loader {
+    static constexpr int RA = 1024 / T::PK;                  // rows a block of a K-major tile holds
+    static constexpr int RB = T::BT ? 4 : RA;                // ... and of the B tile
+    static constexpr int BLK_A = T::A_BYTES / 1024, BLK_B = T::B_BYTES / 1024;   // blocks a tile
+    // the chunk swizzle repeats every two blocks, and a wave's are an even number apart
+    static_assert(T::WAVES % 2 == 0 && BLK_A % 2 == 0 && BLK_B % 2 == 0, "one offset per operand");
     const unsigned char* base[T::IPW];
-    uint32_t off[T::IPW];
+    uint32_t off_a, off_b;
     int64_t b_step;   // bytes between slices of the [K][N] B operand (rows: PK)
 
+    __device__ __forceinline__ static bool is_a(int blk) { return blk < T::NA * BLK_A; }
     // a0, a1 (b0, b1): the tile's first row (column) of the operands, in the
-    // first slice; ops no larger than 2^31 bytes from there (a tile's rows)
+    // first slice
     __device__ __forceinline__ void init(const GemmArgs& a, const uint16_t* a0, const uint16_t* a1,
                                          const uint16_t* b0, const uint16_t* b1, int wave, int lane) {
         b_step = T::BT ? (int64_t)T::BK * a.ldb * 2 : T::PK;
+        auto kmajor = [&](int ld) {   // a lane's row and chunk in its wave's K-major blocks
+            const int lr = lane * 16 / T::PK, slot = lane * 16 % T::PK / 16;
+            const int c = slot ^ (((wave * RA + lr) / T::GK) % T::CPR);
+            return 2u * ((uint32_t)lr * (uint32_t)ld + c * 8);
+        };
+        off_a = kmajor(a.lda);
+        if constexpr (T::BT) {
+            const int lr = lane / 16;
+            off_b = 2u * ((uint32_t)lr * (uint32_t)a.ldb + (uint32_t)((lane % 16) ^ (lr << 2)) * 8);
+        } else {
+            off_b = kmajor(a.ldb);
+        }
 #pragma unroll
         for (int q = 0; q < T::IPW; ++q) {
             const int blk = wave + q * T::WAVES;   // 1 KB block of the stage (wave-uniform)
-            if (blk * 1024 < T::NA * T::A_BYTES) {
-                // K-major A tile: the block holds 1024 / PK whole rows
-                const int t = (blk * 1024) / T::A_BYTES;
-                const int lb = (blk * 1024) % T::A_BYTES + lane * 16;
-                const int r = lb / T::PK, slot = (lb % T::PK) / 16;
-                const int c = slot ^ ((r / T::GK) % T::CPR);
-                base[q] = reinterpret_cast<const unsigned char*>(t ? a1 : a0);
-                off[q] = 2u * ((uint32_t)r * (uint32_t)a.lda + c * 8);
-            } else {
-                const int bb = blk * 1024 - T::NA * T::A_BYTES;
-                const int t = bb / T::B_BYTES;
-                const int lb = bb % T::B_BYTES + lane * 16;
-                base[q] = reinterpret_cast<const unsigned char*>(t ? b1 : b0);
-                if constexpr (T::BT) {
-                    const int r = lb / 256, slot = (lb % 256) / 16;
-                    const int c = slot ^ ((r & 3) << 2);
-                    off[q] = 2u * ((uint32_t)r * (uint32_t)a.ldb + c * 8);
-                } else {
-                    const int r = lb / T::PK, slot = (lb % T::PK) / 16;
-                    const int c = slot ^ ((r / T::GK) % T::CPR);
-                    off[q] = 2u * ((uint32_t)r * (uint32_t)a.ldb + c * 8);
-                }
-            }
+            const int in_b = blk - T::NA * BLK_A;
+            const uint16_t* p = is_a(blk) ? (blk >= BLK_A ? a1 : a0) : (in_b >= BLK_B ? b1 : b0);
+            const int64_t row = is_a(blk) ? (int64_t)(blk % BLK_A) * RA * a.lda : (int64_t)(in_b % BLK_B) * RB * a.ldb;
+            base[q] = reinterpret_cast<const unsigned char*>(p + row);
         }
     }
     __device__ __forceinline__ void load(int q, unsigned char* dst, int wave) const {
-        const unsigned char* src = base[q] + off[q];
-        __builtin_amdgcn_global_load_lds(src, (lds_void*)(dst + (wave + q * T::WAVES) * 1024), 16, 0, 0);
+        const int blk = wave + q * T::WAVES;
+        const unsigned char* src = base[q] + (is_a(blk) ? off_a : off_b);
+        __builtin_amdgcn_global_load_lds(src, (lds_void*)(dst + blk * 1024), 16, 0, 0);
     }
     __device__ __forceinline__ void advance(int wave) {
 #pragma unroll
-        for (int q = 0; q < T::IPW; ++q) {
-            const bool is_a = (wave + q * T::WAVES) * 1024 < T::NA * T::A_BYTES;
-            base[q] += !T::BT || is_a ? (int64_t)T::PK : b_step;
-        }
+        for (int q = 0; q < T::IPW; ++q)
+            base[q] += !T::BT || is_a(wave + q * T::WAVES) ? (int64_t)T::PK : b_step;
     }
 };
 
@@ -424,7 +424,7 @@ __global__ __launch_bounds__(T::THREADS, T::MIN_WAVES) void gemm(GemmArgs a) {
     const int er = lane >> 1;          // epilogue: row (or transposed row) of this lane
     const int ec = (lane & 1) * 16;    // epilogue: 16 consecutive columns
     constexpr bool kPreE0 = EPI == EPI_POLY || EPI == EPI_QPOLY || EPI == EPI_UPDATE || EPI == EPI_FINAL ||
-                            EPI == EPI_APPLY || EPI == EPI_QPOLY_H16 || EPI == EPI_POLY_H16;
+                            EPI == EPI_APPLY || EPI == EPI_APPLY_F32 || EPI == EPI_QPOLY_H16 || EPI == EPI_POLY_H16;
     constexpr bool kPreE1 = EPI == EPI_POLY || EPI == EPI_QPOLY;
     const bool pre = kPreE0 && a.E0 != nullptr && !(EPI == EPI_FINAL && a.out_transposed);
     uint4 e0[T::FM][T::FN][2], e1[T::FM][T::FN][2];
@@ -444,14 +444,17 @@ __global__ __launch_bounds__(T::THREADS, T::MIN_WAVES) void gemm(GemmArgs a) {
             }
     }
 
-    // EPI_APPLY: the W entries this lane updates (16 consecutive bf16 per
+    // EPI_APPLY: the W entries this lane updates (16 consecutive entries per
     // block, row K[p] of W) are fetched before the main loop as well.
     // Addresses are clamped into W so the loads are unconditional; the
     // epilogue uses them only where they are the right entries.
     int32_t wrow[T::FM];
-    uint4 wv[T::FM][T::FN][2];
-    if constexpr (EPI == EPI_APPLY) {
-        const uint16_t* W = a.ms.w<uint16_t>(b);
+    constexpr bool kApply = EPI == EPI_APPLY || EPI == EPI_APPLY_F32;
+    typedef typename std::conditional<EPI == EPI_APPLY_F32, float, uint16_t>::type WT;
+    constexpr int kWQ = 16 * sizeof(WT) / sizeof(uint4);   // 16-byte pieces of 16 entries
+    uint4 wv[T::FM][T::FN][kWQ];
+    if constexpr (kApply) {
+        const WT* W = a.ms.w<WT>(b);
 #pragma unroll
         for (int i = 0; i < T::FM; ++i) {
             const int p = row0 + wm * T::TM + i * 32 + er;
@@ -460,9 +463,9 @@ __global__ __launch_bounds__(T::THREADS, T::MIN_WAVES) void gemm(GemmArgs a) {
             for (int j = 0; j < T::FN; ++j) {
                 int64_t jc = col0 + wn * T::TN + j * 32 + ec;
                 jc = jc + 16 <= a.cols ? jc : a.cols - 16;
-                const uint16_t* src = W + (int64_t)wrow[i] * a.cols + jc;
-                wv[i][j][0] = ldg<uint4>(src);
-                wv[i][j][1] = ldg<uint4>(src + 8);
+                const WT* src = W + (int64_t)wrow[i] * a.cols + jc;
+#pragma unroll
+                for (int q = 0; q < kWQ; ++q) wv[i][j][q] = ldg<uint4>(src + q * (16 / kWQ));
             }
         }
     }
@@ -625,7 +628,7 @@ __global__ __launch_bounds__(T::THREADS, T::MIN_WAVES) void gemm(GemmArgs a) {
             }
             const int64_t orow = transposed ? Cc + er : R + er;
             const int64_t ocol = transposed ? R + ec : Cc + ec;
-            if constexpr (EPI == EPI_UPDATE || EPI == EPI_FINAL || EPI == EPI_APPLY) {
+            if constexpr (EPI == EPI_UPDATE || EPI == EPI_FINAL || kApply) {
                 // + a Z at this lane's 16 entries (none when E0 is null)
                 if (pre) {
                     const uint4 z0 = e0[i][j][0];
@@ -688,31 +691,37 @@ __global__ __launch_bounds__(T::THREADS, T::MIN_WAVES) void gemm(GemmArgs a) {
                     for (int q = 0; q < 16; ++q) v[q] *= ssc;
                 }
             }
-            if constexpr (EPI == EPI_APPLY) {
-                // W[K[p]][j] <- bf16(W[K[p]][j] - lr_eff O[p][j]) (update step, eq. (1))
+            if constexpr (kApply) {
+                // W[K[p]][j] <- round(W[K[p]][j] - lr_eff O[p][j]) (update step, eq. (1))
                 if (orow < a.k) {
-                    uint16_t* w = a.ms.w<uint16_t>(b) + (int64_t)wrow[i] * a.cols + ocol;
+                    WT* w = a.ms.w<WT>(b) + (int64_t)wrow[i] * a.cols + ocol;
+                    auto step = [&](float x, float o) { return __dsub_rn((double)x, __dmul_rn(a.lr_eff, (double)o)); };
                     if (ocol + 16 <= a.d_oth) {
-                        const uint32_t ww[8] = {wv[i][j][0].x, wv[i][j][0].y, wv[i][j][0].z, wv[i][j][0].w,
-                                                wv[i][j][1].x, wv[i][j][1].y, wv[i][j][1].z, wv[i][j][1].w};
-                        uint32_t o[8];
 #pragma unroll
-                        for (int q = 0; q < 8; ++q) {
-                            const double w0 = (double)bf16_bits_to_f32(ww[q] & 0xffffu);
-                            const double w1 = (double)bf16_bits_to_f32(ww[q] >> 16);
-                            o[q] = (uint32_t)f64_to_bf16(__dsub_rn(w0, __dmul_rn(a.lr_eff, (double)v[2 * q]))) |
-                                   ((uint32_t)f64_to_bf16(__dsub_rn(w1, __dmul_rn(a.lr_eff, (double)v[2 * q + 1]))) << 16);
-                        }
-                        stg(w, make_uint4(o[0], o[1], o[2], o[3]));
-                        stg(w + 8, make_uint4(o[4], o[5], o[6], o[7]));
-                    } else {
+                        for (int q = 0; q < kWQ; ++q) {
+                            const uint32_t ww[4] = {wv[i][j][q].x, wv[i][j][q].y, wv[i][j][q].z, wv[i][j][q].w};
+                            uint32_t o[4];
 #pragma unroll
-                        for (int q = 0; q < 16; ++q) {
-                            if (ocol + q < a.d_oth) {
-                                const double x = (double)bf16_bits_to_f32(ldg<uint16_t>(w + q));
-                                stg(w + q, f64_to_bf16(__dsub_rn(x, __dmul_rn(a.lr_eff, (double)v[q]))));
+                            for (int u = 0; u < 4; ++u) {
+                                if constexpr (sizeof(WT) == 2) {
+                                    const int e = 8 * q + 2 * u;
+                                    o[u] = (uint32_t)f64_to_bf16(step(bf16_bits_to_f32(ww[u] & 0xffffu), v[e])) |
+                                           ((uint32_t)f64_to_bf16(step(bf16_bits_to_f32(ww[u] >> 16), v[e + 1])) << 16);
+                                } else {
+                                    o[u] = __float_as_uint((float)step(__uint_as_float(ww[u]), v[4 * q + u]));
+                                }
                             }
+                            stg(w + q * (16 / kWQ), make_uint4(o[0], o[1], o[2], o[3]));
                         }
+                    } else if (ocol < a.d_oth) {
+                        // the row's last entries: all loaded before the first store
+                        float x[16];
+#pragma unroll
+                        for (int q = 0; q < 16; ++q)
+                            if (ocol + q < a.d_oth) x[q] = Elem<WT>::load(w + q);
+#pragma unroll
+                        for (int q = 0; q < 16; ++q)
+                            if (ocol + q < a.d_oth) Elem<WT>::store_f64(w + q, step(x[q], v[q]));
                     }
                     if (a.dbg) {
 #pragma unroll
@@ -1131,7 +1140,8 @@ SymPlan plan_sym(const GemmArgs& a, GemmEpi epi, int npass) {
     return {SYM_128, split && a.K >= 4096 ? parts_of(a, n128, 128, a.M, 256, 1024) : 1};
 }
 
-bool is_sym(GemmEpi epi) { return epi != EPI_UPDATE && epi != EPI_FINAL && epi != EPI_APPLY; }
+bool is_apply(GemmEpi epi) { return epi == EPI_APPLY || epi == EPI_APPLY_F32; }
+bool is_sym(GemmEpi epi) { return epi != EPI_UPDATE && epi != EPI_FINAL && !is_apply(epi); }
 
 // A symmetric product on tile T, whole or split over K.
 template <int NPASS, int EPI, typename T, bool SPLIT = false>
@@ -1176,10 +1186,13 @@ hipError_t sym_three(const GemmArgs& a, const SymPlan& p, hipStream_t s) {
             if constexpr (EPI == EPI_SPLIT) return launch_sym<3, EPI, Tile<3, 0, 256, 256, kSliceK, 2, 4, 2>>(a, 1, s);
             return hipErrorInvalidValue;
         default:
-            // from K = 1024 the slices pay for the run-on loop's longer start
-            // (s = 1024, 16 matrices: 72.3 against 74.7 us; s = 384, 64: 24.8
-            // against 23.1)
-            if (a.K >= 1024) return launch_sym<3, EPI, Tile<3, 0, 128, 128, kSliceK, 4, 2, 2, false, true>>(a, 1, s);
+            // plain products: from K = 1024 the slices pay for the run-on loop's
+            // longer start (s = 1024, 16 matrices: 72.3 against 74.7 us; s =
+            // 384, 64: 24.8 against 23.1); polynomial ones spill in the other
+            // loop within the registers of two blocks a CU (s = 512, 64: 55.4
+            // against 57.2)
+            if (EPI != EPI_SPLIT || a.K >= 1024)
+                return launch_sym<3, EPI, Tile<3, 0, 128, 128, kSliceK, 4, 2, 2, false, true>>(a, 1, s);
             return launch_sym<3, EPI, Tile<3, 0, 128, 128, kSliceK, 4, 2, 2>>(a, 1, s);
     }
 }
@@ -1224,8 +1237,8 @@ hipError_t launch_right(const GemmArgs& a, hipStream_t s) {
         if (a.mreal) r.M = a.mreal;
         return launch_tile<NPASS, EPI, T>(r, s);
     }
-    if constexpr (NPASS == 2 && EPI == EPI_APPLY)
-        return launch_tile<NPASS, EPI, Tile<2, 1, 128, 128, kSliceK, 4, 2, 2>>(a, s);
+    if constexpr ((NPASS == 2 && EPI == EPI_APPLY) || (NPASS < 3 && EPI == EPI_APPLY_F32))
+        return launch_tile<NPASS, EPI, Tile<NPASS, 1, 128, 128, kSliceK, 4, 2, 2>>(a, s);
     else
         return launch_tile<NPASS, EPI, Tile<NPASS, 1, 128, 128, kSliceK, 2, 2, 2>>(a, s);
 }
@@ -1239,7 +1252,7 @@ template <int EPI>
 hipError_t launch_rows(const GemmArgs& a, hipStream_t s) {
     using TR = Tile<1, 0, 256, 256, kSliceK, 2, 4, 3>;
     using TRN = Tile<1, 0, 256, 128, kSliceK, 4, 2, 4>;
-    if constexpr (EPI != EPI_APPLY) {
+    if constexpr (EPI == EPI_UPDATE || EPI == EPI_FINAL) {
         if (a.N % 256 == 0) return launch_tile<1, EPI, TR>(a, s);
     }
     return launch_tile<1, EPI, TRN>(a, s);
@@ -1283,11 +1296,12 @@ __global__ __launch_bounds__(256) void transpose_bf16(const uint16_t* __restrict
 hipError_t launch_gemm(const GemmArgs& a, GemmEpi epi, int npass, hipStream_t s) {
     if (is_sym(epi)) return launch_sym_product(a, epi, npass, s);
     if (a.f16 || a.dual) return hipErrorInvalidValue;
-    if (epi == EPI_APPLY && (a.cols % 8 || a.cols < 16 || a.out_transposed)) return hipErrorInvalidValue;
+    if (is_apply(epi) && (a.cols < 16 || a.out_transposed)) return hipErrorInvalidValue;
     if (a.b_rows) {
         if (npass != 1 || a.M % 256) return hipErrorInvalidValue;
         if (epi == EPI_UPDATE) return launch_rows<EPI_UPDATE>(a, s);
-        return epi == EPI_FINAL ? launch_rows<EPI_FINAL>(a, s) : launch_rows<EPI_APPLY>(a, s);
+        if (epi == EPI_FINAL) return launch_rows<EPI_FINAL>(a, s);
+        return epi == EPI_APPLY ? launch_rows<EPI_APPLY>(a, s) : launch_rows<EPI_APPLY_F32>(a, s);
     }
     if (epi == EPI_UPDATE) return npass == 1 ? launch_right<1, EPI_UPDATE>(a, s) : hipErrorInvalidValue;
     if (epi == EPI_FINAL) {
@@ -1298,6 +1312,10 @@ hipError_t launch_gemm(const GemmArgs& a, GemmEpi epi, int npass, hipStream_t s)
         if (npass == 1) return launch_right<1, EPI_APPLY>(a, s);
         if (npass == 2) return launch_right<2, EPI_APPLY>(a, s);
         if (npass == 3) return launch_right<3, EPI_APPLY>(a, s);
+    } else {
+        if (npass == 1) return launch_right<1, EPI_APPLY_F32>(a, s);
+        if (npass == 2) return launch_right<2, EPI_APPLY_F32>(a, s);
+        if (npass == 3) return launch_right<3, EPI_APPLY_F32>(a, s);
     }
     return hipErrorInvalidValue;
 }

@@ -17,8 +17,6 @@
 // partials, and a second pass folds the row blocks in order. No
 // floating-point atomics anywhere: results are run-to-run bitwise
 // reproducible.
-#include <type_traits>
-
 #include "dion2_device.h"
 
 namespace dion2 {
@@ -48,7 +46,7 @@ __device__ __forceinline__ void wave_reduce(double& hi, double& lo, double& s2) 
 constexpr int kRowsPerBlock = kThreads / 64;
 constexpr int kRowVecs = 8;   // 4-element vectors per lane in flight
 
-template <int VEC, typename GT>
+template <typename GT, bool WHOLE>
 __global__ __launch_bounds__(kThreads) void momentum_rows(MatSet ms, int64_t rows, int64_t cols,
                                                           double* __restrict__ l1,
                                                           double* __restrict__ sq) {
@@ -58,44 +56,53 @@ __global__ __launch_bounds__(kThreads) void momentum_rows(MatSet ms, int64_t row
     if (row >= rows) return;   // whole wave
     float* __restrict__ M = ms.m(b) + row * cols;
     const GT* __restrict__ G = ms.g<GT>(b) + row * cols;
+    typedef typename Quad<GT>::V GRaw;
     // four independent accumulators (element v of each vector goes to set v)
     // keep the fp64 dependency chains short; they are folded in a fixed order
     double h4[4] = {0.0, 0.0, 0.0, 0.0}, l4[4] = {0.0, 0.0, 0.0, 0.0}, q4[4] = {0.0, 0.0, 0.0, 0.0};
-    if constexpr (VEC == 4) {
-        constexpr int kStep = 64 * 4 * kRowVecs;
-        int64_t c = 0;
-        for (; c + kStep <= cols; c += kStep) {
-            float m[kRowVecs][4], g[kRowVecs][4];
+    constexpr int kStep = 64 * 4 * kRowVecs;
+    int64_t c = 0;
+    for (; c + kStep <= cols; c += kStep) {
+        float m[kRowVecs][4], g[kRowVecs][4];
 #pragma unroll
-            for (int u = 0; u < kRowVecs; ++u) {
-                unpack4(ldg_nt<float4>(M + c + (u * 64 + lane) * 4), m[u]);
-                unpack4(ldg_nt<typename std::conditional<sizeof(GT) == 2, uint2, float4>::type>(
-                            G + c + (u * 64 + lane) * 4), g[u]);
-            }
-#pragma unroll
-            for (int u = 0; u < kRowVecs; ++u) {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) m[u][v] = m[u][v] + g[u][v];
-                stg_nt(M + c + (u * 64 + lane) * 4, make_float4(m[u][0], m[u][1], m[u][2], m[u][3]));
-#pragma unroll
-                for (int v = 0; v < 4; ++v) accumulate(fabs((double)m[u][v]), h4[v], l4[v], q4[v]);
-            }
+        for (int u = 0; u < kRowVecs; ++u) {
+            unpack4(ldg_nt<float4>(M + c + (u * 64 + lane) * 4), m[u]);
+            unpack4(ldg_nt<GRaw>(G + c + (u * 64 + lane) * 4), g[u]);
         }
-        for (int64_t cc = c + lane * 4; cc < cols; cc += 64 * 4) {
+#pragma unroll
+        for (int u = 0; u < kRowVecs; ++u) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) m[u][v] = m[u][v] + g[u][v];
+            stg_nt(M + c + (u * 64 + lane) * 4, make_float4(m[u][0], m[u][1], m[u][2], m[u][3]));
+#pragma unroll
+            for (int v = 0; v < 4; ++v) accumulate(fabs((double)m[u][v]), h4[v], l4[v], q4[v]);
+        }
+    }
+    // (WHOLE: the row is whole chunks; the registers of the rest cost 3% there)
+    // the rest of the row, its loads all before its first store (memory
+    // counters retire in issue order); entries past the end count as zero
+    if (!WHOLE && c < cols) {
+        float4 mr[kRowVecs];
+        GRaw gr[kRowVecs];
+#pragma unroll
+        for (int u = 0; u < kRowVecs; ++u) {
+            if (c + u * 256 >= cols) break;   // uniform
+            const int64_t cc = c + (u * 64 + lane) * 4;
+            mr[u] = load_quad(M + cc, cols - cc);
+            gr[u] = load_quad(G + cc, cols - cc);
+        }
+#pragma unroll
+        for (int u = 0; u < kRowVecs; ++u) {
+            if (c + u * 256 >= cols) break;
+            const int64_t cc = c + (u * 64 + lane) * 4;
             float m[4], g[4];
-            load4(M + cc, m);
-            load4(G + cc, g);
+            unpack4(mr[u], m);
+            unpack4(gr[u], g);
 #pragma unroll
             for (int v = 0; v < 4; ++v) m[v] = m[v] + g[v];
-            stg(M + cc, make_float4(m[0], m[1], m[2], m[3]));
+            store_quad(M + cc, make_float4(m[0], m[1], m[2], m[3]), cols - cc);
 #pragma unroll
             for (int v = 0; v < 4; ++v) accumulate(fabs((double)m[v]), h4[v], l4[v], q4[v]);
-        }
-    } else {
-        for (int64_t c = lane; c < cols; c += 64) {
-            const float m = ldg<float>(M + c) + Elem<GT>::load(G + c);
-            stg(M + c, m);
-            accumulate(fabs((double)m), h4[0], l4[0], q4[0]);
         }
     }
     double hi = h4[0], lo = l4[0], s2 = q4[0];
@@ -112,8 +119,8 @@ __global__ __launch_bounds__(kThreads) void momentum_rows(MatSet ms, int64_t row
 }
 
 // Column mode, partial sums of a block of rb_rows rows, kColUnroll rows of a
-// wave loaded at once. With WIDE a block of four waves covers 256 VEC adjacent
-// columns; without, 64 VEC, each wave a contiguous quarter of the rows, and
+// wave loaded at once. With WIDE a block of four waves covers 1024 adjacent
+// columns; without, 256, each wave a contiguous quarter of the rows, and
 // the quarters are folded in row order. Large launches whose rows the wide
 // blocks tile exactly keep them: 4 KB of a row together stream better (16 x
 // 8192 x 2048: 246 against 270 us; 64 x 2048 x 1408, which they do not tile,
@@ -122,56 +129,55 @@ __global__ __launch_bounds__(kThreads) void momentum_rows(MatSet ms, int64_t row
 // 2048 matrix 64 blocks and 145 us, where 64 rows a block take 24.
 constexpr int kColUnroll = 8;
 
-template <int VEC, typename GT, bool WIDE>
+template <typename GT, bool WIDE, bool RAGGED>
 __global__ __launch_bounds__(kThreads) void momentum_cols_partial(MatSet ms, int64_t rows,
                                                                   int64_t cols, int rb_rows,
                                                                   int nrb,
                                                                   double* __restrict__ part) {
+    constexpr int VEC = 4;
     constexpr int kW = WIDE ? 1 : kThreads / 64;   // waves that share a column
     __shared__ double fold[kThreads / 64 - 1][3][VEC][64];
     const int b = blockIdx.z;
     const int rb = blockIdx.y;
     const int lane = threadIdx.x & 63, wave = WIDE ? 0 : threadIdx.x >> 6;
     const int64_t c0 = ((int64_t)blockIdx.x * (WIDE ? kThreads : 64) + (WIDE ? threadIdx.x : lane)) * VEC;
-    const bool in = c0 < cols;
+    const int64_t n = cols - c0;   // columns of this lane that exist
+    const bool in = n > 0;
     const int64_t quarter = rb_rows / kW;
     const int64_t r0 = (int64_t)rb * rb_rows + wave * quarter;
     const int64_t r1 = r0 + quarter < rows ? r0 + quarter : rows;
     const float* __restrict__ M = ms.m(b);
     const GT* __restrict__ G = ms.g<GT>(b);
-    typedef typename std::conditional<VEC == 4, float4, float>::type MRaw;
-    typedef typename std::conditional<VEC == 4, typename std::conditional<sizeof(GT) == 2, uint2, float4>::type,
-                                      GT>::type GRaw;
+    typedef typename Quad<GT>::V GRaw;
     double hi[VEC], lo[VEC], s2[VEC];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) hi[v] = lo[v] = s2[v] = 0.0;
-    auto add = [&](const MRaw& mr, const GRaw& gr) {
+    auto add = [&](const float4& mr, const GRaw& gr) {
         float m[VEC], g[VEC];
-        if constexpr (VEC == 4) {
-            unpack4(mr, m);
-            unpack4(gr, g);
-        } else {
-            m[0] = mr;
-            if constexpr (sizeof(GT) == 2) g[0] = bf16_bits_to_f32(gr);
-            else g[0] = gr;
-        }
+        unpack4(mr, m);
+        unpack4(gr, g);
 #pragma unroll
         for (int v = 0; v < VEC; ++v) accumulate(fabs((double)(m[v] + g[v])), hi[v], lo[v], s2[v]);
     };
-    if (in) {
+    if (in) {   // (the loads of lanes with four columns need no other branch)
         int64_t r = r0;
         for (; r + kColUnroll <= r1; r += kColUnroll) {
-            MRaw m[kColUnroll];
+            float4 m[kColUnroll];
             GRaw g[kColUnroll];
 #pragma unroll
             for (int u = 0; u < kColUnroll; ++u) {
-                m[u] = ldg_nt<MRaw>(M + (r + u) * cols + c0);
-                g[u] = ldg_nt<GRaw>(G + (r + u) * cols + c0);
+                if constexpr (RAGGED) {
+                    m[u] = load_quad(M + (r + u) * cols + c0, n);
+                    g[u] = load_quad(G + (r + u) * cols + c0, n);
+                } else {
+                    m[u] = ldg_nt<float4>(M + (r + u) * cols + c0);
+                    g[u] = ldg_nt<GRaw>(G + (r + u) * cols + c0);
+                }
             }
 #pragma unroll
             for (int u = 0; u < kColUnroll; ++u) add(m[u], g[u]);
         }
-        for (; r < r1; ++r) add(ldg_nt<MRaw>(M + r * cols + c0), ldg_nt<GRaw>(G + r * cols + c0));
+        for (; r < r1; ++r) add(load_quad<RAGGED>(M + r * cols + c0, n), load_quad<RAGGED>(G + r * cols + c0, n));
     }
     if (wave > 0) {
 #pragma unroll
@@ -191,9 +197,11 @@ __global__ __launch_bounds__(kThreads) void momentum_cols_partial(MatSet ms, int
             dd_add(hi[v], lo[v], fold[w][0][v][lane], fold[w][1][v][lane]);
             s2[v] += fold[w][2][v][lane];
         }
-        out[c0 + v] = hi[v];
-        out[cols + c0 + v] = lo[v];
-        out[2 * cols + c0 + v] = s2[v];
+        if (!RAGGED || v < n) {
+            out[c0 + v] = hi[v];
+            out[cols + c0 + v] = lo[v];
+            out[2 * cols + c0 + v] = s2[v];
+        }
     }
 }
 
@@ -237,24 +245,26 @@ __global__ __launch_bounds__(kThreads) void momentum_cols_final(const double* __
     sq[(int64_t)b * cols + c] = s2;
 }
 
-template <int VEC, typename GT>
+template <typename GT>
 hipError_t launch_typed(const MomentumArgs& a, int axis, hipStream_t s) {
     if (axis == 0) {
         dim3 grid((unsigned)((a.rows + kRowsPerBlock - 1) / kRowsPerBlock), (unsigned)a.batch);
-        hipLaunchKernelGGL((momentum_rows<VEC, GT>), grid, dim3(kThreads), 0, s, a.ms, a.rows,
-                           a.cols, a.l1, a.sq);
+        if (a.cols % (64 * 4 * kRowVecs) == 0)
+            hipLaunchKernelGGL((momentum_rows<GT, true>), grid, dim3(kThreads), 0, s, a.ms, a.rows, a.cols, a.l1, a.sq);
+        else
+            hipLaunchKernelGGL((momentum_rows<GT, false>), grid, dim3(kThreads), 0, s, a.ms, a.rows, a.cols, a.l1, a.sq);
     } else {
-        const bool wide = a.cols % ((int64_t)kThreads * VEC) == 0 &&
-                          a.cols / (kThreads * VEC) * a.nrb * a.batch >= 1024;
-        const int64_t per_block = (wide ? kThreads : 64) * VEC;
+        constexpr int64_t kWideCols = kThreads * 4;
+        const bool wide = a.cols % kWideCols == 0 && a.cols / kWideCols * a.nrb * a.batch >= 1024;
+        const int64_t per_block = wide ? kWideCols : 256;
         dim3 grid((unsigned)((a.cols + per_block - 1) / per_block), (unsigned)a.nrb,
                   (unsigned)a.batch);
-        if (wide)
-            hipLaunchKernelGGL((momentum_cols_partial<VEC, GT, true>), grid, dim3(kThreads), 0, s, a.ms,
-                               a.rows, a.cols, a.rb_rows, a.nrb, a.part);
-        else
-            hipLaunchKernelGGL((momentum_cols_partial<VEC, GT, false>), grid, dim3(kThreads), 0, s, a.ms,
-                               a.rows, a.cols, a.rb_rows, a.nrb, a.part);
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, a.ms, a.rows, a.cols, a.rb_rows, a.nrb, a.part);
+        };
+        if (wide) launch(momentum_cols_partial<GT, true, false>);
+        else if (a.cols % 4) launch(momentum_cols_partial<GT, false, true>);
+        else launch(momentum_cols_partial<GT, false, false>);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         dim3 grid2((unsigned)((a.cols + kFoldCols - 1) / kFoldCols), (unsigned)a.batch);
@@ -271,8 +281,7 @@ hipError_t launch_typed(const MomentumArgs& a, int axis, hipStream_t s) {
 // of fewer than four blocks a compute unit halves them, down to 32 rows, as
 // long as the partials fit in part_bytes.
 int64_t momentum_col_blocks(int64_t rows, int64_t cols, int batch, size_t part_bytes, int* rb_rows) {
-    const int64_t vec = cols % 4 == 0 ? 4 : 1;
-    const int64_t strips = (cols + 64 * vec - 1) / (64 * vec) * batch;
+    const int64_t strips = (cols + 255) / 256 * batch;
     auto blocks = [&](int rb) { return (rows + rb - 1) / rb; };
     int rb = 256;
     while (rb > 32 && strips * blocks(rb) < 1024 &&
@@ -283,11 +292,7 @@ int64_t momentum_col_blocks(int64_t rows, int64_t cols, int batch, size_t part_b
 }
 
 hipError_t launch_momentum(const MomentumArgs& a, int axis, int g_bf16, hipStream_t s) {
-    const bool vec = (a.cols % 4) == 0;
-    if (g_bf16) {
-        return vec ? launch_typed<4, uint16_t>(a, axis, s) : launch_typed<1, uint16_t>(a, axis, s);
-    }
-    return vec ? launch_typed<4, float>(a, axis, s) : launch_typed<1, float>(a, axis, s);
+    return g_bf16 ? launch_typed<uint16_t>(a, axis, s) : launch_typed<float>(a, axis, s);
 }
 
 }  // namespace dion2
