@@ -311,12 +311,15 @@ __global__ __launch_bounds__(kThreads) void apply_cols_strip(ApplyArgs a) {
 // staged in LDS once per block. A row whose length is not a multiple of 8
 // (`ragged`) ends in part of a chunk. The first 64 KT ranks of a row are fetched
 // with the row (one row ahead); larger k take further passes of 64 KT.
-constexpr int kSelRows = 32;                 // rows per block (8 per wave)
+// Rows per block: 32 (8 a wave) where that gives two blocks a compute unit;
+// a launch of fewer halves them down to one row a wave, since a wave's rows
+// are a serial chain of loads and stores (3 x 1155 x 771 fp32: 16.1 us in 111
+// blocks, 11.6 in 867).
 constexpr int kSelRowBytes = 8192;           // LDS row buffer per wave
 constexpr int kSelMaxK = 4096;               // k <= cols <= 4096 (bf16) or 2048 (fp32)
 
 template <typename WT, int NCH, int KT>
-__global__ __launch_bounds__(kThreads) void apply_cols_sel(ApplyArgs a) {
+__global__ __launch_bounds__(kThreads) void apply_cols_sel(ApplyArgs a, int block_rows) {
     __shared__ __attribute__((aligned(16))) WT row_s[4][kSelRowBytes / sizeof(WT)];
     extern __shared__ int32_t sel_s[];   // k entries (dynamic: k * 4 bytes)
     const int b = blockIdx.y;
@@ -372,9 +375,9 @@ __global__ __launch_bounds__(kThreads) void apply_cols_sel(ApplyArgs a) {
             o[t] = ldg<float>(src + (p < a.k ? p : a.k - 1));
         }
     };
-    const int64_t r_end = (int64_t)(blockIdx.x + 1) * kSelRows < a.rows ? (int64_t)(blockIdx.x + 1) * kSelRows
-                                                                         : a.rows;
-    int64_t r = (int64_t)blockIdx.x * kSelRows + wave;
+    const int64_t r_next = (int64_t)(blockIdx.x + 1) * block_rows;
+    const int64_t r_end = r_next < a.rows ? r_next : a.rows;
+    int64_t r = (int64_t)blockIdx.x * block_rows + wave;
     if (r >= r_end) return;   // whole wave; no block barrier follows
     Chunk8<WT> w[NCH], wn[NCH];
     float o[KT], on[KT];
@@ -425,11 +428,13 @@ __global__ __launch_bounds__(kThreads) void apply_cols_sel(ApplyArgs a) {
 
 template <typename WT, int NCH>
 void launch_cols_sel_k(const ApplyArgs& a, hipStream_t s) {
-    dim3 grid((unsigned)((a.rows + kSelRows - 1) / kSelRows), (unsigned)a.batch);
+    int block_rows = 32;
+    while (block_rows > 4 && (a.rows + block_rows - 1) / block_rows * a.batch < 512) block_rows /= 2;
+    dim3 grid((unsigned)((a.rows + block_rows - 1) / block_rows), (unsigned)a.batch);
     const size_t lds = (size_t)a.k * sizeof(int32_t);   // K's copy; the row buffers are static
-    if (a.k <= 256) hipLaunchKernelGGL((apply_cols_sel<WT, NCH, 4>), grid, dim3(kThreads), lds, s, a);
-    else if (a.k <= 512) hipLaunchKernelGGL((apply_cols_sel<WT, NCH, 8>), grid, dim3(kThreads), lds, s, a);
-    else hipLaunchKernelGGL((apply_cols_sel<WT, NCH, 16>), grid, dim3(kThreads), lds, s, a);
+    if (a.k <= 256) hipLaunchKernelGGL((apply_cols_sel<WT, NCH, 4>), grid, dim3(kThreads), lds, s, a, block_rows);
+    else if (a.k <= 512) hipLaunchKernelGGL((apply_cols_sel<WT, NCH, 8>), grid, dim3(kThreads), lds, s, a, block_rows);
+    else hipLaunchKernelGGL((apply_cols_sel<WT, NCH, 16>), grid, dim3(kThreads), lds, s, a, block_rows);
 }
 
 template <typename WT>
