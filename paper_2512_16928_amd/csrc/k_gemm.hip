@@ -1131,12 +1131,14 @@ SymPlan plan_sym(const GemmArgs& a, GemmEpi epi, int npass) {
     // 288 to 336 tiles of 64 x 64 measured 13.6 us at K = 2048 where 128 x 128
     // took 19.5, 22.6 against 32.8 at 4096; 528 of them 23.9 against 20.7
     if (n64 <= 448 && a.K < 8192) return {SYM_64, 1};
-    if (a.f16) return {a.M >= 2048 && n256 > 0 ? SYM_256 : SYM_128, 1};
     // 256 x 256 tiles run one to a compute unit: they pay once their last
     // round is filled well (s = 2048: 144 tiles 57.8 against 62.0 us, 288
-    // tiles 116.6 against 104.6; s = 1024, 160 tiles: 201 against 215)
+    // tiles 116.6 against 104.6; s = 1024, 160 tiles: 201 against 215, 120
+    // tiles 95.8 against 74.4; s = 4096, 136 tiles, where 128 x 128 would take
+    // just over a round of 512: a Muon step of 1756 against 1883 us)
     const int64_t rounds = (n256 + 255) / 256;
-    if (a.M >= 1024 && n256 >= (rounds == 1 ? 140 : 160 * rounds)) return {SYM_256, 1};
+    if (a.M >= (a.f16 ? 2048 : 1024) && n256 >= (rounds > 1 ? 160 * rounds : n128 > 512 ? 129 : 140))
+        return {SYM_256, 1};
     return {SYM_128, split && a.K >= 4096 ? parts_of(a, n128, 128, a.M, 256, 1024) : 1};
 }
 
@@ -1247,9 +1249,12 @@ hipError_t launch_right(const GemmArgs& a, hipStream_t s) {
 // on the wide plain-read tiles (28% faster at s = 2048, 35% at 4096 than the
 // transposing reads of the [K][N] operand): 256 x 256, or 256 x 128 where l
 // is not a multiple of 256 and for the fused update step (whose W rows spill
-// on 256 x 256).
+// on 256 x 256). A launch of fewer than 160 of the former (two of the latter)
+// leaves too much of the chip idle and takes 128 x 128.
 template <int EPI>
 hipError_t launch_rows(const GemmArgs& a, hipStream_t s) {
+    if ((int64_t)a.batch * (a.M / 256) * (a.N / 128) < 2 * 160)
+        return launch_tile<1, EPI, Tile<1, 0, 128, 128, kSliceK, 2, 2, 4>>(a, s);
     using TR = Tile<1, 0, 256, 256, kSliceK, 2, 4, 3>;
     using TRN = Tile<1, 0, 256, 128, kSliceK, 4, 2, 4>;
     if constexpr (EPI == EPI_UPDATE || EPI == EPI_FINAL) {

@@ -91,3 +91,16 @@ def test_column_norm_blocks(hip_device, rows, cols, batch, gdt):
     res = run_gpu(Wn, Mn, Gn, 0.02, axis=AXIS_COLS, ns_steps=1)
     check_matrix(res, batch - 1, 0.02, ns_steps=1, axis=AXIS_COLS)
     assert bool((res["norms"] == res["norms"][0]).all())
+
+
+def test_direct_rows_on_small_tiles(hip_device):
+    """DIRECT's X-side products with X^T as rows: 128 x 128 tiles for one
+    matrix, 256 x 256 for a batch, bitwise the same; and against the oracle."""
+    W, M, G = workloads.make_group(one_group_workload(2048, 2304, name="rows2048"), 0, hip_device)
+    W4, M4, G4 = (t.repeat(4, 1, 1) for t in (W, M, G))
+    res = run_gpu(W, M, G, 1.0)
+    check_matrix(res, 0, 1.0)
+    binding.dion2_step_strided(W4, M4, G4, 1.0)
+    torch.cuda.synchronize()
+    want = res["W"][0].view(torch.int16)
+    assert all(torch.equal(W4[i].cpu().view(torch.int16), want) for i in range(4))
