@@ -828,181 +828,168 @@ __global__ __launch_bounds__(256) void reduce_parts(GemmArgs a) {
 
 // ---- the GRAM chain of a compact matrix with s <= 64, in one block
 //
-// The s x s matrices stay in LDS as bf16 hi / lo planes of 64 rows (pitch
-// kSmallPitch entries: 144-byte rows put the 32 rows of a fragment read on
+// The s x s matrices stay in LDS as bf16 hi / lo pairs, four hi and their four
+// lo entries side by side (16 bytes: what a lane reads or writes at once), in
+// 64 rows of 272 bytes (the 16-byte pieces of 16 rows fall on
 // distinct banks). Every product is the one the launch-per-product chain
 // makes: per 16-deep k-step hi*lo, lo*hi, then hi*hi into fp32
 // accumulators, the same epilogue arithmetic and hi / lo split, and exactly
 // symmetric storage (entries on and above the diagonal computed, mirrored
-// below it). Entries past s_k are never read.
+// below it). The MFMAs are v_mfma_f32_16x16x16_bf16, whose sums equal those of
+// v_mfma_f32_32x32x16_bf16 bit for bit. Entries past s_k are never read.
 //
-// Bound by latency: fourteen dependent stages of one to two products, each
-// 12 dependent MFMAs between LDS reads and writes. So the code is one
-// product's (a second copy would be fetched cold into the instruction cache
-// of a kernel that runs once), a stage's two products go to different waves,
-// and the stores are 8 bytes wide where a lane holds four entries of a row:
-// 28.0 us before, with separate copies and 2-byte stores, 16.2 us now (five
-// steps, s = 64).
-constexpr int kSmallPitch = 72;
-constexpr int kSmallPlane = kSmallChainS * kSmallPitch;
-enum { SP_A = 0, SP_Q = 2, SP_T = 4, SP_P = 6, SP_PLANES = 10 };   // hi, lo; P twice (6 and 8)
+// Bound by latency: fourteen dependent stages of one to two products, each a
+// chain of 12 dependent MFMAs between LDS reads and writes. So a wave takes
+// one 16 x 16 block of a stage's products (ten waves for s = 64: a chain step
+// of 16 cycles instead of 64, and a quarter of a 32 x 32 block's conversions
+// and stores), a stage's two products share x and interleave, and the code is
+// one stage's (a second copy would be fetched cold into the instruction cache
+// of a kernel that runs once). Five steps at s = 64: 28.0 us with copies of
+// the code on 32 x 32 blocks, 16.2 with one copy, 12.9 now (s = 32: 7.7).
+constexpr int kSmallPitch = 2 * kSmallChainS + 8;
+constexpr int kSmallMat = kSmallChainS * kSmallPitch;
+enum { SM_A, SM_Q, SM_T, SM_P, SM_COUNT = SM_P + 2 };   // P twice
 
-// dst = x y (x, y symmetric, given by rows) on the 32 x 32 block of rows
-// bi and columns bj, by one wave; qpoly: dst = c x y + b x + a I (x = y =
-// A_t). An MFMA lane holds one column's entries of four row quads, that is
-// 8-byte pieces of the mirrored block's rows. Of the block above the diagonal
-// one wave computes it and stores the mirror, and another computes the
-// transposed block (operands swapped, bitwise the same sums) and stores it
-// (`swap`). A block on the diagonal is stored mirrored whole, then its
-// entries above the diagonal are stored over it.
-// The fragments of x stay in xh, xl: `fresh` says that x is another one, or
-// the same plane rewritten.
-template <int KS>
-__device__ __forceinline__ void small_product(uint16_t* pl, int x, int y, int dst, bool qpoly, int bi, int bj,
-                                              bool swap, int lane, float ca, float cb, float cc, bool fresh,
-                                              bf16x8 (&xh)[KS / 16], bf16x8 (&xl)[KS / 16]) {
-    constexpr int NK = KS / 16;
-    const uint16_t* xr = pl + x * kSmallPlane + (bi * 32 + (lane & 31)) * kSmallPitch + 8 * (lane >> 5);
-    const uint16_t* yr = pl + y * kSmallPlane + (bj * 32 + (lane & 31)) * kSmallPitch + 8 * (lane >> 5);
-    bf16x8 yh[NK], yl[NK];
-    if (fresh) {
-#pragma unroll
-        for (int k = 0; k < NK; ++k) {
-            xh[k] = *reinterpret_cast<const bf16x8*>(xr + 16 * k);
-            xl[k] = *reinterpret_cast<const bf16x8*>(xr + kSmallPlane + 16 * k);
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < NK; ++k) {
-        yh[k] = *reinterpret_cast<const bf16x8*>(yr + 16 * k);
-        yl[k] = *reinterpret_cast<const bf16x8*>(yr + kSmallPlane + 16 * k);
-    }
-    // where this lane's entries go: row n, columns m0 + 8 q .. m0 + 8 q + 3
-    const int n = (swap ? bi : bj) * 32 + (lane & 31);
-    const int m0 = (swap ? bj : bi) * 32 + 4 * (lane >> 5);
-    const int at = n * kSmallPitch + m0;
-    uint2 eh[4], el[4];   // A there (it is symmetric)
-    if (qpoly) {
-        const uint16_t* xp = pl + x * kSmallPlane + at;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            eh[q] = *reinterpret_cast<const uint2*>(xp + 8 * q);
-            el[q] = *reinterpret_cast<const uint2*>(xp + kSmallPlane + 8 * q);
-        }
-    }
-    f32x16 acc;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    if (swap) {
-#pragma unroll
-        for (int k = 0; k < NK; ++k) {
-            acc = mfma32(yl[k], xh[k], acc);
-            acc = mfma32(yh[k], xl[k], acc);
-            acc = mfma32(yh[k], xh[k], acc);
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < NK; ++k) {
-            acc = mfma32(xh[k], yl[k], acc);
-            acc = mfma32(xl[k], yh[k], acc);
-            acc = mfma32(xh[k], yh[k], acc);
-        }
-    }
-    if (qpoly) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            float a0[4], a1[4];
-            unpack4(eh[q], a0);
-            unpack4(el[q], a1);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                float v = cb * (a0[u] + a1[u]) + cc * acc[4 * q + u];
-                if (m0 + 8 * q + u == n) v += ca;
-                acc[4 * q + u] = v;
-            }
-        }
-    }
-    uint16_t* oh = pl + dst * kSmallPlane;
-    uint2 h[4], l[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        h[q] = make_uint2(pack2(acc[4 * q], acc[4 * q + 1]), pack2(acc[4 * q + 2], acc[4 * q + 3]));
-        float hf[4];
-        unpack4(h[q], hf);
-        l[q] = make_uint2(pack2(acc[4 * q] - hf[0], acc[4 * q + 1] - hf[1]),
-                          pack2(acc[4 * q + 2] - hf[2], acc[4 * q + 3] - hf[3]));
-        *reinterpret_cast<uint2*>(oh + at + 8 * q) = h[q];
-        *reinterpret_cast<uint2*>(oh + kSmallPlane + at + 8 * q) = l[q];
-    }
-    if (bi == bj) {
-        // LDS accesses of one wave complete in issue order. Lanes at or below
-        // the diagonal store into their row's padding instead of branching.
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const uint32_t hw[2] = {h[q].x, h[q].y}, lw[2] = {l[q].x, l[q].y};
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int m = m0 + 8 * q + u;
-                uint16_t* o = oh + (m < n ? m * kSmallPitch + n : n * kSmallPitch + kSmallChainS);
-                o[0] = (uint16_t)(hw[u >> 1] >> (16 * (u & 1)));
-                o[kSmallPlane] = (uint16_t)(lw[u >> 1] >> (16 * (u & 1)));
-            }
-        }
-    }
+// where entry (r, c)'s hi half lies; its lo half is 4 further on
+__device__ __forceinline__ constexpr int small_at(int r, int c) { return r * kSmallPitch + (c >> 2) * 8 + (c & 3); }
+
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+__device__ __forceinline__ f32x4 mfma16(i16x4 a, i16x4 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
 }
 
-// Waves 0 .. 3 compute a stage's first product (blocks (0,0), (1,1), (0,1)
-// and its transposed twin; with KS = 32 wave 0 alone), waves 4 .. 7 its second.
-constexpr int kSmallThreads = 512;
-
 template <int KS>
-__global__ __launch_bounds__(kSmallThreads) void chain_small(SmallChainArgs a) {
-    __shared__ __attribute__((aligned(16))) uint16_t pl[SP_PLANES * kSmallPlane];
+__global__ __launch_bounds__(64 * (KS / 16) * (KS / 16 + 1) / 2) void chain_small(SmallChainArgs a) {
+    constexpr int NK = KS / 16;                       // k-steps, and blocks a side
+    constexpr int THREADS = 64 * NK * (NK + 1) / 2;   // a wave per block on or above the diagonal
+    __shared__ __attribute__((aligned(16))) uint16_t pl[SM_COUNT * kSmallMat];
     const int b = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t s2 = a.s_pad * a.s_pad;
-    constexpr int kChunks = KS * (KS / 8);   // 16-byte pieces of [0, KS)^2, per plane
-    for (int i = tid; i < 2 * kChunks; i += kSmallThreads) {
-        const int plane = i / kChunks, r = (i % kChunks) / (KS / 8), c = i % (KS / 8);
-        const uint16_t* src = (plane ? a.Al : a.Ah) + (int64_t)b * s2 + (int64_t)r * a.s_pad + 8 * c;
-        *reinterpret_cast<uint4*>(pl + (SP_A + plane) * kSmallPlane + r * kSmallPitch + 8 * c) = ldg<uint4>(src);
+    constexpr int kChunks = KS * (KS / 8);   // 8 entries of [0, KS)^2
+    for (int i = tid; i < kChunks; i += THREADS) {
+        const int r = i / (KS / 8), c = 8 * (i % (KS / 8));
+        const int64_t at = (int64_t)b * s2 + (int64_t)r * a.s_pad + c;
+        const uint4 h = ldg<uint4>(a.Ah + at), l = ldg<uint4>(a.Al + at);
+        uint16_t* o = pl + SM_A * kSmallMat + small_at(r, c);
+        *reinterpret_cast<uint4*>(o) = make_uint4(h.x, h.y, l.x, l.y);
+        *reinterpret_cast<uint4*>(o + 8) = make_uint4(h.z, h.w, l.z, l.w);
     }
+    // this wave's block: rows 16 bi, columns 16 bj, bi <= bj
+    int bi = 0, bj = wave;
+    while (bj >= NK - bi) {
+        bj -= NK - bi;
+        ++bi;
+    }
+    bj += bi;
+    // A lane's fragments: 4 consecutive k of row lane & 15 of the block's rows
+    // of x (columns: rows of y); its results: entries (m .. m + 3, n), stored
+    // as 8 bytes of row n (the mirror) and one by one in column n. On the
+    // diagonal the mirror is stored whole and the entries above the diagonal
+    // over it; those on or below go to the row's padding instead.
+    const int xat = small_at(16 * bi + (lane & 15), 4 * (lane >> 4));
+    const int yat = small_at(16 * bj + (lane & 15), 4 * (lane >> 4));
+    const int m = 16 * bi + 4 * (lane >> 4), n = 16 * bj + (lane & 15);
+    const int mirror = small_at(n, m);
+    int direct[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) direct[u] = m + u < n ? small_at(m + u, n) : small_at(n, kSmallChainS);
+
+    struct Pair {
+        i16x4 h, l;
+    };
+    Pair x[NK];
+    auto read = [&](int mat, int at, Pair (&f)[NK]) {
+#pragma unroll
+        for (int k = 0; k < NK; ++k)
+            f[k] = __builtin_bit_cast(Pair, *reinterpret_cast<const uint4*>(pl + mat * kSmallMat + at + 32 * k));
+    };
+    auto store = [&](int mat, const f32x4& v) {
+        uint16_t* o = pl + mat * kSmallMat;
+        const uint2 h = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
+        float hf[4];
+        unpack4(h, hf);
+        const uint2 l = make_uint2(pack2(v[0] - hf[0], v[1] - hf[1]), pack2(v[2] - hf[2], v[3] - hf[3]));
+        *reinterpret_cast<uint4*>(o + mirror) = make_uint4(h.x, h.y, l.x, l.y);
+        __builtin_amdgcn_wave_barrier();   // LDS accesses of one wave complete in issue order
+        const uint32_t hw[2] = {h.x, h.y}, lw[2] = {l.x, l.y};
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            o[direct[u]] = (uint16_t)(hw[u >> 1] >> (16 * (u & 1)));
+            o[direct[u] + 4] = (uint16_t)(lw[u >> 1] >> (16 * (u & 1)));
+        }
+    };
     __syncthreads();
-    const int w = wave & 3, second = wave >> 2;
-    const int bi = w == 1 ? 1 : 0, bj = w == 0 ? 0 : 1;
-    const bool mine = KS > 32 || w == 0;
     int cur = 0;
-    bf16x8 xh[KS / 16], xl[KS / 16];
     // per step: Q_t (the first one is P itself); T = Q_t A (t < T - 1) and
     // P <- Q_t P (t > 0); A <- Q_t T (t < T - 1)
     for (int t = 0; t < a.ns_steps; ++t) {
         const float ca = a.cf[t][0], cb = a.cf[t][1], cc = a.cf[t][2];
         const bool do_p = t > 0, do_t = t + 1 < a.ns_steps;
-        const int q = t == 0 ? SP_P : SP_Q;
-        // the second stage's second product, and whether it is due
-        const int y1 = second ? SP_P + 2 * cur : SP_A, dst1 = second ? SP_P + 2 * (1 - cur) : SP_T;
-        const bool due1 = second ? do_p : do_t;
+        const int q = t == 0 ? SM_P : SM_Q;
+        const int pin = SM_P + cur, pout = SM_P + 1 - cur;
         const int stages = do_t ? 3 : 2;
 #pragma unroll 1
         for (int stage = 0; stage < stages; ++stage) {
-            const int x = stage == 0 ? SP_A : q;
-            const int y = stage == 0 ? SP_A : stage == 1 ? y1 : SP_T;
-            const int dst = stage == 0 ? q : stage == 1 ? dst1 : SP_A;
-            if (mine && (stage == 1 ? due1 : !second))
-                small_product<KS>(pl, x, y, dst, stage == 0, bi, bj, w == 3, lane, ca, cb, cc, stage < 2, xh,
-                                  xl);   // the third stage's x is the second's
+            const bool poly = stage == 0, two = stage == 1 && do_p && do_t;
+            const int y0 = stage == 2 ? SM_T : stage == 1 && !do_t ? pin : SM_A;
+            const int d0 = stage == 0 ? q : stage == 2 ? SM_A : do_t ? SM_T : pout;
+            if (stage < 2) read(stage == 0 ? SM_A : q, xat, x);   // the third stage's x is the second's
+            Pair y[NK];
+            read(y0, yat, y);
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+            if (two) {
+                Pair z[NK];
+                read(pin, yat, z);
+                f32x4 acp = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int k = 0; k < NK; ++k) {
+                    acc = mfma16(x[k].h, y[k].l, acc);
+                    acp = mfma16(x[k].h, z[k].l, acp);
+                    acc = mfma16(x[k].l, y[k].h, acc);
+                    acp = mfma16(x[k].l, z[k].h, acp);
+                    acc = mfma16(x[k].h, y[k].h, acc);
+                    acp = mfma16(x[k].h, z[k].h, acp);
+                }
+                store(pout, acp);
+            } else {
+                uint4 e;   // A at this lane's entries (it is symmetric)
+                if (poly) e = *reinterpret_cast<const uint4*>(pl + SM_A * kSmallMat + mirror);
+#pragma unroll
+                for (int k = 0; k < NK; ++k) {
+                    acc = mfma16(x[k].h, y[k].l, acc);
+                    acc = mfma16(x[k].l, y[k].h, acc);
+                    acc = mfma16(x[k].h, y[k].h, acc);
+                }
+                if (poly) {
+                    float a0[4], a1[4];
+                    unpack4(make_uint2(e.x, e.y), a0);
+                    unpack4(make_uint2(e.z, e.w), a1);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        float v = cb * (a0[u] + a1[u]) + cc * acc[u];
+                        if (m + u == n) v += ca;
+                        acc[u] = v;
+                    }
+                }
+            }
+            // (a stage never writes a plane that it reads, but for A <- Q T,
+            // whose A has been read by the stages before)
+            store(d0, acc);
             __syncthreads();
         }
         if (do_p) cur = 1 - cur;
     }
     // P_T out
-    const uint16_t* ph = pl + (SP_P + 2 * cur) * kSmallPlane;
-    for (int i = tid; i < 2 * kChunks; i += kSmallThreads) {
-        const int plane = i / kChunks, r = (i % kChunks) / (KS / 8), c = i % (KS / 8);
-        stg((plane ? a.Pl : a.Ph) + (int64_t)b * s2 + (int64_t)r * a.s_pad + 8 * c,
-            *reinterpret_cast<const uint4*>(ph + plane * kSmallPlane + r * kSmallPitch + 8 * c));
+    for (int i = tid; i < kChunks; i += THREADS) {
+        const int r = i / (KS / 8), c = 8 * (i % (KS / 8));
+        const uint16_t* o = pl + (SM_P + cur) * kSmallMat + small_at(r, c);
+        const uint4 p0 = *reinterpret_cast<const uint4*>(o), p1 = *reinterpret_cast<const uint4*>(o + 8);
+        const int64_t at = (int64_t)b * s2 + (int64_t)r * a.s_pad + c;
+        stg(a.Ph + at, make_uint4(p0.x, p0.y, p1.x, p1.y));
+        stg(a.Pl + at, make_uint4(p0.z, p0.w, p1.z, p1.w));
     }
 }
 
@@ -1329,8 +1316,8 @@ hipError_t launch_chain_small(const SmallChainArgs& a, hipStream_t s) {
     if (a.s_k < 32 || a.s_k > kSmallChainS || a.s_k % 32 || a.s_pad < kSmallChainS || a.s_pad % 8 ||
         a.ns_steps < 1 || a.ns_steps > kChainMaxSteps || a.batch < 1)
         return hipErrorInvalidValue;
-    if (a.s_k == 32) hipLaunchKernelGGL(chain_small<32>, dim3((unsigned)a.batch), dim3(kSmallThreads), 0, s, a);
-    else hipLaunchKernelGGL(chain_small<64>, dim3((unsigned)a.batch), dim3(kSmallThreads), 0, s, a);
+    if (a.s_k == 32) hipLaunchKernelGGL(chain_small<32>, dim3((unsigned)a.batch), dim3(64 * 3), 0, s, a);
+    else hipLaunchKernelGGL(chain_small<64>, dim3((unsigned)a.batch), dim3(64 * 10), 0, s, a);
     return hipGetLastError();
 }
 
