@@ -1096,28 +1096,35 @@ SymPlan plan_sym(const GemmArgs& a, GemmEpi epi, int npass) {
     const int64_t n64 = sym_tiles(a, mr, 64), n128 = sym_tiles(a, a.M, 128);
     const int64_t n256 = a.M % 256 ? 0 : sym_tiles(a, a.M, 256);
     if (npass == 3) {
-        // one block a compute unit: four stages; up to 560 blocks two or
-        // three of the two-stage ring's share one (544 at s = 1024: 26.8
-        // against 30.4 us; 1152 at s = 512: 29.8 against 28.2; 576 at s =
-        // 512 16.7 against 17.9 alone, but the grouped call of the 1B stack,
-        // whose other groups use the same caches, 0.6% slower)
+        // one block a compute unit: four stages; beyond, two or three of the
+        // two-stage ring's share one, as long as they are few: up to 512 (495
+        // at s = 640: 20.8 against 22.3 us; 408 at s = 1024: 20.0 against 27.7;
+        // 544 there 25.2 against 24.6), 560 where K is at most 512 (640 at s =
+        // 256: 13.6 against 11.4; 576 at s = 512: 15.2 against 15.6 alone, but
+        // the grouped call of the 1B stack, whose other groups use the same
+        // caches, 0.6% slower), and on a single 128 x 128 tile, of which they
+        // are three quarters, up to 1600 (384 at s = 128: 5.8 against 7.5 us;
+        // 1536: 15.1 against 17.0)
         if (n64 <= 256) return {SYM_64, split && a.K >= 1024 ? parts_of(a, n64, 64, mr, 256, 512) : 1};
-        if (n64 <= 560) return {SYM_64S2, 1};
+        if (n64 <= (mr <= 128 ? 1600 : a.K <= 512 ? 560 : 512)) return {SYM_64S2, 1};
         // two rounds of 256 x 256 tiles for the plain products (the
         // polynomial epilogues spill on them): 5-10% at s = 1024 and 2048
         const bool poly = epi == EPI_POLY || epi == EPI_QPOLY;
         return {!poly && a.M >= 1024 && n256 >= 512 ? SYM_256 : SYM_128, 1};
     }
-    if (n64 <= 256) {
+    if (n64 <= 256 && (n64 <= 170 || a.K < 6144)) {
         // below K = 2048 the second launch costs more than the shorter loop
         // saves (1024 deep: 6.4 against 7.5 us); from 4096 on two blocks a
-        // compute unit pay (1024 x 4096: 15.6 us in three parts, 18.0 whole)
-        const int64_t most = a.K >= 4096 && n64 > 128 ? 512 : 256;
+        // compute unit pay (1024 x 4096: 15.6 us in three parts, 18.0 whole),
+        // but not in two parts (768 x 4096, 234 tiles: 27.8, 23.1 whole)
+        const int64_t most = a.K >= 4096 && n64 > 128 && n64 <= 170 ? 512 : 256;
         return {SYM_64, split && a.K >= 2048 ? parts_of(a, n64, 64, mr, most, 640) : 1};
     }
     // 288 to 336 tiles of 64 x 64 measured 13.6 us at K = 2048 where 128 x 128
-    // took 19.5, 22.6 against 32.8 at 4096; 528 of them 23.9 against 20.7
-    if (n64 <= 448 && a.K < 8192) return {SYM_64, 1};
+    // took 19.5, 22.6 against 32.8 at 4096; 528 of them 23.9 against 20.7. A
+    // longer K goes in parts of 128 x 128 tiles (384 x 10240, 210 tiles of 64 x
+    // 64: 31.0 us in four parts, 62.9 whole, 69.6 in two of 64 x 64)
+    if (n64 <= 448 && a.K < 6144) return {SYM_64, 1};
     // 256 x 256 tiles run one to a compute unit: they pay once their last
     // round is filled well (s = 2048: 144 tiles 57.8 against 62.0 us, 288
     // tiles 116.6 against 104.6; s = 1024, 160 tiles: 201 against 215, 120
