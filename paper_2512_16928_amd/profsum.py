@@ -97,14 +97,19 @@ def phase_of(kernel: str):
         return "ns_update"
     if k.startswith("chain_small"):  # the whole s x s chain of s <= 64 in one launch
         return "ns_poly"
-    m = re.match(r"gemm<(\d+), (?:\(dion2::GemmEpi\))?(\d)", k)
+    if k.startswith("reduce_parts"): # the sum over the parts of a Gram product's K
+        return "ns_gram"
+    m = re.match(r"gemm<(\d+), (?:\(dion2::GemmEpi\))?(\d+)", k)
     if m:
         npass, epi = int(m.group(1)), int(m.group(2))
-        if epi in (2, 3, 5):         # update / final product with X (5: with the update step)
+        if epi in (2, 3, 5, 10):     # update / final product with X (5, 10: with the update step)
             return "ns_update"
+        if epi == 9:                 # part of K of a Gram product (no other product is split)
+            return "ns_gram"
         # X X^T: one pass on bf16 operands, stored as a hi / lo pair (0) or in
         # fp16 (6); the same epilogues on fp16 operands are s x s products
-        f16_tile = re.search(r"Tile<[^>]*\btrue>", k) is not None
+        # (Tile's ninth parameter; a tenth, the main loop's form, may follow)
+        f16_tile = re.search(r"Tile<(?:\d+, ){8}true\b", k) is not None
         if epi in (0, 6) and npass == 1 and not f16_tile:
             return "ns_gram"
         return "ns_poly"             # the s x s products

@@ -29,6 +29,14 @@ def test_phase_of_kernel_names():
         "void dion2::(anonymous namespace)::gemm<1, 2, dion2::(anonymous namespace)::Tile<1, 1, 128, 128, 32, 2, 2, 2>, false>(dion2::GemmArgs)": "ns_update",
         "void dion2::(anonymous namespace)::gemm<2, 3, dion2::(anonymous namespace)::Tile<2, 1, 128, 128, 32, 2, 2, 2>, false>(dion2::GemmArgs)": "ns_update",
         "void dion2::(anonymous namespace)::gemm<2, 5, dion2::(anonymous namespace)::Tile<2, 1, 128, 128, 32, 2, 2, 2>, false>(dion2::GemmArgs)": "ns_update",
+        "void dion2::(anonymous namespace)::gemm<1, 6, dion2::(anonymous namespace)::Tile<1, 0, 128, 128, 32, 2, 2, 4, true, true>, true>(dion2::GemmArgs)": "ns_poly",
+        "void dion2::(anonymous namespace)::gemm<1, 6, dion2::(anonymous namespace)::Tile<1, 0, 64, 64, 64, 2, 2, 4, true, false>, true>(dion2::GemmArgs)": "ns_poly",
+        "void dion2::(anonymous namespace)::gemm<1, 0, dion2::(anonymous namespace)::Tile<1, 0, 128, 128, 32, 2, 2, 4, false, true>, true>(dion2::GemmArgs)": "ns_gram",
+        "void dion2::(anonymous namespace)::gemm<1, 9, dion2::(anonymous namespace)::Tile<1, 0, 64, 64, 64, 2, 2, 4, false, false>, true>(dion2::GemmArgs)": "ns_gram",
+        "void dion2::(anonymous namespace)::reduce_parts<0, dion2::(anonymous namespace)::Tile<1, 0, 64, 64, 64, 2, 2, 4, false, false> >(dion2::GemmArgs)": "ns_gram",
+        "void dion2::(anonymous namespace)::gemm<2, 10, dion2::(anonymous namespace)::Tile<2, 1, 128, 128, 32, 4, 2, 2, false, false>, false>(dion2::GemmArgs)": "ns_update",
+        "void dion2::(anonymous namespace)::chain_small<64>(dion2::SmallChainArgs)": "ns_poly",
+        "void dion2::(anonymous namespace)::select_reg<1024, 2>(dion2::SelectArgs)": "select",
         "dion2::transpose_bf16(unsigned short const*, unsigned short*, long, long, long)": "ns_update",
         "dion2::(anonymous namespace)::colpass_compact(dion2::ColpassArgs)": "gather",
         "dion2::(anonymous namespace)::colpass_fold(dion2::ColpassArgs)": "gather",
