@@ -453,9 +453,9 @@ double sym_flops(double s, double inner) { return s * (s + 1.0) * inner; }
 
 // `scratch` (the O buffer, free until the final product) takes the partial
 // sums of a Gram product whose long inner side is split over more blocks.
-// s_real: the side the s x s matrices are needed to, 0 for all of s_pad (a
-// chain shared by groups reads further than a narrower member's own side).
-GemmArgs gram_args(const Plan& P, const uint16_t* Z, uint16_t* hi, uint16_t* lo, float* scratch, int64_t s_real) {
+// s_chain: the side the s x s products run to (a chain shared by groups reads
+// further than a narrower member's own side).
+GemmArgs gram_args(const Plan& P, const uint16_t* Z, uint16_t* hi, uint16_t* lo, float* scratch, int64_t s_chain) {
     GemmArgs g{};
     g.batch = P.batch;
     g.A0 = g.B0 = Z;
@@ -467,7 +467,8 @@ GemmArgs gram_args(const Plan& P, const uint16_t* Z, uint16_t* hi, uint16_t* lo,
     g.out1 = lo;
     g.sOut0 = g.sOut1 = P.s_pad * P.s_pad;
     g.ldo0 = g.ldo1 = (int)P.s_pad;
-    g.mreal = (int)round_up(s_real, 64);
+    g.mreal = (int)round_up(P.s_k, 64);
+    g.mfill = (int)round_up(s_chain, 64);
     g.part = scratch;
     g.part_floats = (int64_t)P.batch * P.s_pad * P.l_pad;
     return g;
@@ -643,14 +644,14 @@ hipError_t ns_direct(const Plan& P, uint16_t* Z0, uint16_t* Z1, uint16_t* const*
 // A_0 = Z Z^T as a hi / lo pair, or in fp16 (scaled) for the fp16 chain.
 // With Zlo (the fp32 master) Z is the pair Z + Zlo: three passes.
 hipError_t gram_a0(const Plan& P, const uint16_t* Z, const uint16_t* Zlo, uint16_t* Ah, uint16_t* Al, float* O,
-                   int64_t s_real, const ChainFmt& fmt, hipStream_t stream) {
+                   int64_t s_chain, const ChainFmt& fmt, hipStream_t stream) {
     const double s_r = (double)(P.k < P.d_oth ? P.k : P.d_oth);
     const double l_r = (double)(P.k < P.d_oth ? P.d_oth : P.k);
     const double nb = (double)P.batch;
     const int npass = Zlo ? 3 : 1;
     // Z in (hi, and lo), A out (hi + lo, or fp16)
     const double gram_bytes = ((Zlo ? 4.0 : 2.0) * s_r * l_r + (fmt.f16 ? 2.0 : 4.0) * s_r * s_r) * nb;
-    GemmArgs g = gram_args(P, Z, Ah, fmt.f16 ? nullptr : Al, O, s_real);
+    GemmArgs g = gram_args(P, Z, Ah, fmt.f16 ? nullptr : Al, O, s_chain);
     if (fmt.f16) g.oexp = fmt.eA;
     if (Zlo) g.A1 = g.B1 = Zlo;
     const GemmEpi epi = fmt.f16 ? EPI_H16 : EPI_SPLIT;
@@ -1545,7 +1546,7 @@ int groups_impl(const dion2_group* groups, int ngroups, float alpha, float mu, f
         fins[g] = make_final(P, ms, b, lr, ns_steps, gopt[g]);
         if (c >= 0) {
             e = gram_a0(P, b.Z0, P.master ? b.Z1 : nullptr, b.sbuf[SQ_AHI], b.sbuf[SQ_ALO], b.O,
-                        0, chain_fmt_for(fmt, chains[c].f16), s);
+                        chains[c].s_k, chain_fmt_for(fmt, chains[c].f16), s);
             if (e != hipSuccess) return hip_fail(e, "launch K4 Gram");
             if (nS > 1) {
                 e = hipEventRecord(ev_a0[g], s);

@@ -360,11 +360,16 @@ struct GemmArgs {
     // fp16 Gram-form chain: fp16 operands, and the scale exponents above
     int f16;
     int oexp, oexpx, eexp, sexp;
-    // the rows (of a symmetric product also the columns) the output is needed
-    // to, a multiple of 64 (0: all of M). Tiles past them may be left
-    // unwritten: nothing in them reaches a real entry, since every sum over s
-    // stops there.
+    // the rows (of a symmetric product also the columns) that are real, rounded
+    // up to 64 (0: all of M). Output past them may be left unwritten: nothing in
+    // it reaches a real entry, since every sum over s stops there. Tiles and
+    // the split of K are chosen from this side alone, so a matrix's sums are
+    // the same in a shared chain as in its own.
     int mreal;
+    // symmetric products: the side the output must be defined to (zeros past
+    // mreal), a multiple of 64 and at least mreal (0: mreal); a shared chain's,
+    // whose sums run to its widest member's side
+    int mfill;
     // symmetric products whose K launch_gemm may split: scratch of part_floats
     // fp32 values for the partial sums (null: never split), and the parts
     float* part;

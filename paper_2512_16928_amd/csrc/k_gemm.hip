@@ -755,7 +755,8 @@ __global__ __launch_bounds__(T::THREADS, T::MIN_WAVES) void gemm(GemmArgs a) {
 // C = the sum over the parts of K, in their order, of a product computed by
 // EPI_PART launches, in EPI's output form and exactly symmetric, as gemm's
 // own epilogue stores it. A wave takes one 32 x 32 block of a tile; blocks
-// below the diagonal are the mirrors of others. Bound by latency: a launch
+// below the diagonal are the mirrors of others, tiles past the side that the
+// parts cover (a.M) are zeros out to a.mfill. Bound by latency: a launch
 // of few tiles has a few MB of partials, which its own loads fetch at once.
 template <int EPI, typename T>
 __global__ __launch_bounds__(256) void reduce_parts(GemmArgs a) {
@@ -764,8 +765,10 @@ __global__ __launch_bounds__(256) void reduce_parts(GemmArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     constexpr int PER = (T::BM / 32) * (T::BN / 32);   // blocks of a tile
     static_assert(PER % 4 == 0, "a block of four waves stays inside one tile");
-    const int tiles = a.M / T::BM;
+    const int tiles = a.mfill / T::BM;                    // written, a side
     const int ntile = tiles * (tiles + 1) / 2;
+    const int ptiles = a.M / T::BM;                       // of which there are parts
+    const int nptile = ptiles * (ptiles + 1) / 2;
     const int64_t w = (int64_t)blockIdx.x * 4 + wave;
     const int blk = (int)(w % PER);
     const int tile = (int)(w / PER % ntile);
@@ -778,13 +781,15 @@ __global__ __launch_bounds__(256) void reduce_parts(GemmArgs a) {
     const int R = I * T::BM + 32 * (blk / (T::BN / 32));
     const int C = (I + rem) * T::BN + 32 * (blk % (T::BN / 32));
     if (R > C) return;   // whole wave; no block barrier follows
-    const float* in = a.part + ((int64_t)b * a.ksplit * ntile + tile) * (T::BM * T::BN) + blk * 1024 + lane * 4;
-    const int64_t step = (int64_t)ntile * (T::BM * T::BN);
+    const int ptile = I * ptiles - I * (I - 1) / 2 + rem;   // the tile's place among the parts'
+    const float* in = a.part + ((int64_t)b * a.ksplit * nptile + ptile) * (T::BM * T::BN) + blk * 1024 + lane * 4;
+    const int64_t step = (int64_t)nptile * (T::BM * T::BN);
+    const int nparts = I + rem < ptiles ? a.ksplit : 0;
     float v[16];
 #pragma unroll
     for (int q = 0; q < 16; ++q) v[q] = 0.f;
     int p = 0;
-    for (; p + 4 <= a.ksplit; p += 4) {   // sixteen loads in flight
+    for (; p + 4 <= nparts; p += 4) {   // sixteen loads in flight
         float4 x[4][4];
 #pragma unroll
         for (int u = 0; u < 4; ++u)
@@ -800,7 +805,7 @@ __global__ __launch_bounds__(256) void reduce_parts(GemmArgs a) {
                 v[4 * q + 3] += x[u][q].w;
             }
     }
-    for (; p < a.ksplit; ++p) {
+    for (; p < nparts; ++p) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const float4 x = ldg<float4>(in + p * step + q * 256);
@@ -1044,7 +1049,7 @@ template <int NPASS, int EPI, typename T>
 hipError_t launch_split(const GemmArgs& a, hipStream_t s) {
     const hipError_t e = launch_tile<NPASS, EPI_PART, T, true>(a, s);
     if (e != hipSuccess) return e;
-    const int64_t tiles = a.M / T::BM;
+    const int64_t tiles = a.mfill / T::BM;
     const int64_t waves = (int64_t)a.batch * (tiles * (tiles + 1) / 2) * (T::BM / 32) * (T::BN / 32);
     hipLaunchKernelGGL((reduce_parts<EPI, T>), dim3((unsigned)(waves / 4)), dim3(256), 0, s, a);
     return hipGetLastError();
@@ -1143,7 +1148,12 @@ bool is_sym(GemmEpi epi) { return epi != EPI_UPDATE && epi != EPI_FINAL && !is_a
 template <int NPASS, int EPI, typename T, bool SPLIT = false>
 hipError_t launch_sym(const GemmArgs& a0, int ksplit, hipStream_t s) {
     GemmArgs a = a0;
-    if (T::BM == 64 && a.mreal) a.M = a.N = a.mreal;
+    if (T::BM == 64 && a.mreal) {
+        a.mfill = std::max(a.mreal, a.mfill);
+        a.M = a.N = ksplit > 1 ? a.mreal : a.mfill;
+    } else {
+        a.mfill = a.M;
+    }
     a.K = (a.K + T::BK - 1) / T::BK * T::BK;   // operands are zero to the next 128
     a.ksplit = ksplit;
     if constexpr (SPLIT && (EPI == EPI_SPLIT || EPI == EPI_H16)) {

@@ -104,3 +104,39 @@ def test_direct_rows_on_small_tiles(hip_device):
     torch.cuda.synchronize()
     want = res["W"][0].view(torch.int16)
     assert all(torch.equal(W4[i].cpu().view(torch.int16), want) for i in range(4))
+
+
+@pytest.mark.parametrize("shapes,kw", [
+    ([(520, 4096, 8)], {}),                       # s = 130: three 64-tiles a side of the four padded, 5 parts
+    ([(520, 4096, 8), (1000, 1100, 1)], {}),      # beside a wider member (s = 250): zeros past its own side
+    ([(540, 8192, 4), (800, 2700, 3)], {}),       # s = 135 and 200, both split, the second over 64-tile rows of its own
+    ([(256, 4096, 40)], {}),                      # s = 64: into the one-launch chain, one tile of four
+    ([(768, 3072, 12), (1000, 4096, 1)], dict(ns_chain=CHAIN_F16)),    # into the fp16 chain
+    ([(640, 1040, 20), (1020, 1040, 1)], dict(ns_master=MASTER_FP32)),  # three passes, split from K = 1024
+])
+def test_split_k_in_grouped_calls(hip_device, shapes, kw):
+    """A Gram product split over K is cut alike in a grouped call, whose shared
+    chain may need A_0 further than the group's own side: bitwise the per-group
+    calls. Every group here but the one 1100 long is split (two launches a Gram
+    product)."""
+    wl = workloads.Workload("gsplit", "test", tuple(workloads.Group(f"g{i}", *s) for i, s in enumerate(shapes)), (0.25,))
+    stacks = [workloads.make_group(wl, i, hip_device) for i in range(len(shapes))]
+    solo = [tuple(t.clone() for t in st) for st in stacks]
+
+    def gram_launches(call):
+        binding.dion2_profile_reset()
+        binding.dion2_profile_enable(True)
+        call()
+        torch.cuda.synchronize()
+        prof = binding.dion2_profile_read()
+        binding.dion2_profile_enable(False)
+        return prof["ns_gram"]["launches"]
+
+    for W, M, G in solo:
+        want = 2 if W.shape[-1] != 1100 else 1
+        assert gram_launches(lambda: binding.dion2_step_ex(W, M, G, 0.25, **kw)) == want
+    binding.dion2_step_groups([(W, M, G, AXIS_AUTO) for W, M, G in stacks], 0.25, **kw)
+    torch.cuda.synchronize()
+    for i, ((W, M, _), (Ws, Ms, _)) in enumerate(zip(stacks, solo)):
+        assert torch.equal(M, Ms), f"group {i}: momentum"
+        assert torch.equal(W.view(torch.int16), Ws.view(torch.int16)), f"group {i}: weights"
