@@ -45,8 +45,19 @@ __device__ __forceinline__ void wave_reduce(double& hi, double& lo, double& s2) 
 
 constexpr int kRowsPerBlock = kThreads / 64;
 constexpr int kRowVecs = 8;   // 4-element vectors per lane in flight
+constexpr int64_t kRowChunk = 64 * 4 * kRowVecs;   // entries of a row a wave takes at once
 
-template <typename GT, bool WHOLE>
+// What a row has past its whole chunks is taken one vector at a time through
+// the caches, or (BATCHED) with all its loads before its first store, past
+// the caches like the chunks and for any length. Through the caches wins
+// behind whole chunks, until a launch's rests together, about 1.3 GB, outgrow
+// them (us, cached and BATCHED: 8 x 4096 x 11008 681 and 709, 32 x 2000 x 4000
+// 453 and 459; 64 x 2000 x 3584 837 and 815), and for rows of one or two vectors
+// in a launch that the 256 MB last-level cache about holds (200 x 256 x 256: the
+// step 77 and 83; 1000 x 256 x 256 331 and 327). BATCHED wins on rows between,
+// where one vector at a time is a chain of up to eight waits (64 x 1000 x 2000
+// 234 and 211, 1 x 1000 x 2000 11 and 8.5).
+template <typename GT, bool BATCHED>
 __global__ __launch_bounds__(kThreads) void momentum_rows(MatSet ms, int64_t rows, int64_t cols,
                                                           double* __restrict__ l1,
                                                           double* __restrict__ sq) {
@@ -60,9 +71,8 @@ __global__ __launch_bounds__(kThreads) void momentum_rows(MatSet ms, int64_t row
     // four independent accumulators (element v of each vector goes to set v)
     // keep the fp64 dependency chains short; they are folded in a fixed order
     double h4[4] = {0.0, 0.0, 0.0, 0.0}, l4[4] = {0.0, 0.0, 0.0, 0.0}, q4[4] = {0.0, 0.0, 0.0, 0.0};
-    constexpr int kStep = 64 * 4 * kRowVecs;
     int64_t c = 0;
-    for (; c + kStep <= cols; c += kStep) {
+    for (; c + kRowChunk <= cols; c += kRowChunk) {
         float m[kRowVecs][4], g[kRowVecs][4];
 #pragma unroll
         for (int u = 0; u < kRowVecs; ++u) {
@@ -78,10 +88,19 @@ __global__ __launch_bounds__(kThreads) void momentum_rows(MatSet ms, int64_t row
             for (int v = 0; v < 4; ++v) accumulate(fabs((double)m[u][v]), h4[v], l4[v], q4[v]);
         }
     }
-    // (WHOLE: the row is whole chunks; the registers of the rest cost 3% there)
-    // the rest of the row, its loads all before its first store (memory
-    // counters retire in issue order); entries past the end count as zero
-    if (!WHOLE && c < cols) {
+    if constexpr (!BATCHED) {   // the row's length is a multiple of 4
+        for (int64_t cc = c + lane * 4; cc < cols; cc += 64 * 4) {
+            float m[4], g[4];
+            load4(M + cc, m);
+            load4(G + cc, g);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) m[v] = m[v] + g[v];
+            stg(M + cc, make_float4(m[0], m[1], m[2], m[3]));
+#pragma unroll
+            for (int v = 0; v < 4; ++v) accumulate(fabs((double)m[v]), h4[v], l4[v], q4[v]);
+        }
+    } else if (c < cols) {
+        // (memory counters retire in issue order); entries past the end count as zero
         float4 mr[kRowVecs];
         GRaw gr[kRowVecs];
 #pragma unroll
@@ -249,10 +268,13 @@ template <typename GT>
 hipError_t launch_typed(const MomentumArgs& a, int axis, hipStream_t s) {
     if (axis == 0) {
         dim3 grid((unsigned)((a.rows + kRowsPerBlock - 1) / kRowsPerBlock), (unsigned)a.batch);
-        if (a.cols % (64 * 4 * kRowVecs) == 0)
-            hipLaunchKernelGGL((momentum_rows<GT, true>), grid, dim3(kThreads), 0, s, a.ms, a.rows, a.cols, a.l1, a.sq);
-        else
+        const int64_t lines = a.rows * a.batch;
+        const bool cached = a.cols >= kRowChunk ? lines * (a.cols % kRowChunk) <= int64_t(1) << 27
+                                                : a.cols <= 512 && lines * a.cols <= int64_t(1) << 25;
+        if (a.cols % 4 == 0 && cached)
             hipLaunchKernelGGL((momentum_rows<GT, false>), grid, dim3(kThreads), 0, s, a.ms, a.rows, a.cols, a.l1, a.sq);
+        else
+            hipLaunchKernelGGL((momentum_rows<GT, true>), grid, dim3(kThreads), 0, s, a.ms, a.rows, a.cols, a.l1, a.sq);
     } else {
         constexpr int64_t kWideCols = kThreads * 4;
         const bool wide = a.cols % kWideCols == 0 && a.cols / kWideCols * a.nrb * a.batch >= 1024;

@@ -12,7 +12,7 @@ import pytest
 import torch
 
 from paper_2512_16928_amd import binding, workloads
-from paper_2512_16928_amd.binding import AXIS_AUTO, AXIS_COLS, CHAIN_F16, MASTER_FP32, NS_DIRECT, NS_GRAM, SELECT_RANDOM
+from paper_2512_16928_amd.binding import AXIS_AUTO, AXIS_COLS, AXIS_ROWS, CHAIN_F16, MASTER_FP32, NS_DIRECT, NS_GRAM, SELECT_RANDOM
 from test_gpu_parity import check_matrix, one_group_workload, run_gpu
 
 pytestmark = pytest.mark.gpu
@@ -140,3 +140,25 @@ def test_split_k_in_grouped_calls(hip_device, shapes, kw):
     for i, ((W, M, _), (Ws, Ms, _)) in enumerate(zip(stacks, solo)):
         assert torch.equal(M, Ms), f"group {i}: momentum"
         assert torch.equal(W.view(torch.int16), Ws.view(torch.int16)), f"group {i}: weights"
+
+
+@pytest.mark.parametrize("rows,cols,batches", [
+    (64, 512, (1, 3)),        # short rows, through the caches
+    (65, 516, (1, 3)),        # past them, not whole vectors a lane
+    (33, 2052, (1, 2)),       # one vector behind a chunk
+    (40, 4092, (1, 2)),       # a rest one vector short of a chunk
+    (1024, 4092, (1, 70)),    # the launch's rests past 2^27 entries
+    (512, 508, (1, 130)),     # short rows past 2^25 entries
+])
+def test_row_norm_rests(hip_device, rows, cols, batches):
+    """The rest of a row past its whole chunks, by either loop of the row norms:
+    exact norms, momentum and selection; bitwise the same whatever the batch."""
+    W, M, G = workloads.make_group(one_group_workload(rows, cols, axis=AXIS_ROWS, name=f"rest{rows}x{cols}"), 0, hip_device)
+    res = run_gpu(W.clone(), M.clone(), G, 0.05, axis=AXIS_ROWS, ns_steps=1)
+    check_matrix(res, 0, 0.05, ns_steps=1, axis=AXIS_ROWS)
+    for n in batches[1:]:
+        Wn, Mn, Gn = (t.repeat(n, 1, 1) for t in (W, M, G))
+        norms = torch.empty((n, rows), dtype=torch.float64, device=hip_device)
+        binding.dion2_step_ex(Wn, Mn, Gn, 0.05, ns_steps=1, axis=AXIS_ROWS, dbg_norms=norms)
+        torch.cuda.synchronize()
+        assert bool((norms.cpu() == res["norms"][0]).all()) and bool((Mn == res["M"][0].to(hip_device)).all())
