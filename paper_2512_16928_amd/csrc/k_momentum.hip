@@ -137,29 +137,76 @@ __global__ __launch_bounds__(kThreads) void momentum_rows(MatSet ms, int64_t row
     }
 }
 
-// Column mode, partial sums of a block of rb_rows rows, kColUnroll rows of a
-// wave loaded at once. With WIDE a block of four waves covers 1024 adjacent
-// columns; without, 256, each wave a contiguous quarter of the rows, and
-// the quarters are folded in row order. Large launches whose rows the wide
-// blocks tile exactly keep them: 4 KB of a row together stream better (16 x
-// 8192 x 2048: 246 against 270 us; 64 x 2048 x 1408, which they do not tile,
-// 191 us on the narrow ones against 222 on single waves). Bound by memory once enough rows are in flight: the row blocks shrink with
-// the launch (momentum_col_blocks), since 256 rows a thread left one 8192 x
-// 2048 matrix 64 blocks and 145 us, where 64 rows a block take 24.
+// Column mode, partial sums of a block of rb_rows rows; the row blocks shrink
+// with the launch (momentum_col_blocks), since 256 rows a thread left one 8192
+// x 2048 matrix 64 blocks and 145 us, where 64 rows a block take 24.
+//
+// From about three waves a SIMD on (kStreamWaves), rows of whole vectors: a wave
+// streams 256 columns down the whole row block, a row at a time; the waves,
+// not the loads of one, cover the latency, and the registers must leave room
+// for eight a SIMD. Blocks of four adjacent waves where they tile the row, else
+// of one. Bound by memory: 16 x 8192 x 2048 242 us, 256 x 2048 x 1408 741; with
+// a wave's eight rows in flight, as below, 261 and 771. (5 x 11008 x 4096, 3440
+// waves: 231 with the fold, 241 below.)
+constexpr int64_t kStreamWaves = 3328;
+
+int64_t stream_waves(int64_t cols, int64_t nrb, int batch) { return (cols + 255) / 256 * nrb * batch; }
+
+template <typename GT>
+__global__ __launch_bounds__(kThreads) void momentum_cols_stream(MatSet ms, int64_t rows, int64_t cols, int rb_rows,
+                                                                 int nrb, double* __restrict__ part) {
+    constexpr int VEC = 4;
+    const int b = blockIdx.z;
+    const int rb = blockIdx.y;
+    const int64_t c0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * VEC;
+    if (c0 >= cols) return;
+    const int64_t r0 = (int64_t)rb * rb_rows;
+    const int64_t r1 = r0 + rb_rows < rows ? r0 + rb_rows : rows;
+    const float* __restrict__ M = ms.m(b);
+    const GT* __restrict__ G = ms.g<GT>(b);
+    double hi[VEC], lo[VEC], s2[VEC];
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) hi[v] = lo[v] = s2[v] = 0.0;
+#pragma unroll 4
+    for (int64_t r = r0; r < r1; ++r) {
+        const float* p = M + r * cols + c0;
+        const GT* q = G + r * cols + c0;
+        float m[VEC], g[VEC];
+        unpack4(ldg_nt<float4>(p), m);
+        unpack4(ldg_nt<typename Quad<GT>::V>(q), g);
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) m[v] = m[v] + g[v];
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) accumulate(fabs((double)m[v]), hi[v], lo[v], s2[v]);
+    }
+    double* out = part + ((int64_t)b * nrb + rb) * 3 * cols;
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) {
+        out[c0 + v] = hi[v];
+        out[cols + c0 + v] = lo[v];
+        out[2 * cols + c0 + v] = s2[v];
+    }
+}
+
+// Smaller launches: a block covers 256 columns, each wave a contiguous quarter
+// of the rows, kColUnroll of them loaded at once, and the quarters are folded
+// in row order (3072 waves of the other kernel, us with it and here: 64 x 2048 x
+// 1408 226 and 190, 12 x 8192 x 2048 216 and 203; 2048 waves, 8 x 8192 x 2048:
+// 182 and 131).
 constexpr int kColUnroll = 8;
 
-template <typename GT, bool WIDE, bool RAGGED>
+template <typename GT, bool RAGGED>
 __global__ __launch_bounds__(kThreads) void momentum_cols_partial(MatSet ms, int64_t rows,
                                                                   int64_t cols, int rb_rows,
                                                                   int nrb,
                                                                   double* __restrict__ part) {
     constexpr int VEC = 4;
-    constexpr int kW = WIDE ? 1 : kThreads / 64;   // waves that share a column
-    __shared__ double fold[kThreads / 64 - 1][3][VEC][64];
+    constexpr int kW = kThreads / 64;   // waves that share a column
+    __shared__ double fold[kW - 1][3][VEC][64];
     const int b = blockIdx.z;
     const int rb = blockIdx.y;
-    const int lane = threadIdx.x & 63, wave = WIDE ? 0 : threadIdx.x >> 6;
-    const int64_t c0 = ((int64_t)blockIdx.x * (WIDE ? kThreads : 64) + (WIDE ? threadIdx.x : lane)) * VEC;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t c0 = ((int64_t)blockIdx.x * 64 + lane) * VEC;
     const int64_t n = cols - c0;   // columns of this lane that exist
     const bool in = n > 0;
     const int64_t quarter = rb_rows / kW;
@@ -206,7 +253,7 @@ __global__ __launch_bounds__(kThreads) void momentum_cols_partial(MatSet ms, int
             fold[wave - 1][2][v][lane] = s2[v];
         }
     }
-    if constexpr (!WIDE) __syncthreads();
+    __syncthreads();
     if (wave > 0 || !in) return;
     double* out = part + ((int64_t)b * nrb + rb) * 3 * cols;
 #pragma unroll
@@ -224,22 +271,23 @@ __global__ __launch_bounds__(kThreads) void momentum_cols_partial(MatSet ms, int
     }
 }
 
-// The row blocks folded in order: a block takes 16 columns, sixteen groups of
-// threads a contiguous share of the row blocks each, and the shares are
-// folded in order. Latency-bound: one thread a column over 32 row blocks took
-// 12 us.
-constexpr int kFoldCols = 16;
-constexpr int kFoldWays = kThreads / kFoldCols;
-
+// The row blocks folded in order: WAYS groups of threads of a block take a
+// contiguous share of the row blocks each, and the shares are folded in
+// order. Latency-bound in small launches (one thread a column over 32 row
+// blocks took 12 us, sixteen take 4); a launch with blocks enough folds a
+// column by one thread, coalesced and without the second stage (256 x 2048 x
+// 1408: 17.9 us with sixteen, 11.7 with one; 64 x 2048 x 1408: 8.1 with
+// sixteen, 5.2 with four).
+template <int WAYS>
 __global__ __launch_bounds__(kThreads) void momentum_cols_final(const double* __restrict__ part,
                                                                 int nrb, int64_t cols,
                                                                 double* __restrict__ l1,
                                                                 double* __restrict__ sq) {
-    __shared__ double fold[3][kFoldWays][kFoldCols];
+    constexpr int kCols = kThreads / WAYS;
     const int b = blockIdx.y;
-    const int cl = threadIdx.x % kFoldCols, way = threadIdx.x / kFoldCols;
-    const int64_t c = (int64_t)blockIdx.x * kFoldCols + cl;
-    const int per = (nrb + kFoldWays - 1) / kFoldWays;
+    const int cl = threadIdx.x % kCols, way = threadIdx.x / kCols;
+    const int64_t c = (int64_t)blockIdx.x * kCols + cl;
+    const int per = (nrb + WAYS - 1) / WAYS;
     const int q0 = way * per < nrb ? way * per : nrb;
     const int q1 = q0 + per < nrb ? q0 + per : nrb;
     double hi = 0.0, lo = 0.0, s2 = 0.0;
@@ -251,15 +299,19 @@ __global__ __launch_bounds__(kThreads) void momentum_cols_final(const double* __
             s2 += p[2 * cols];
         }
     }
-    fold[0][way][cl] = hi;
-    fold[1][way][cl] = lo;
-    fold[2][way][cl] = s2;
-    __syncthreads();
-    if (way > 0 || c >= cols) return;
-    for (int w = 1; w < kFoldWays; ++w) {
-        dd_add(hi, lo, fold[0][w][cl], fold[1][w][cl]);
-        s2 += fold[2][w][cl];
+    if constexpr (WAYS > 1) {
+        __shared__ double fold[3][WAYS][kCols];
+        fold[0][way][cl] = hi;
+        fold[1][way][cl] = lo;
+        fold[2][way][cl] = s2;
+        __syncthreads();
+        if (way > 0) return;
+        for (int w = 1; w < WAYS; ++w) {
+            dd_add(hi, lo, fold[0][w][cl], fold[1][w][cl]);
+            s2 += fold[2][w][cl];
+        }
     }
+    if (c >= cols) return;
     l1[(int64_t)b * cols + c] = hi + lo;
     sq[(int64_t)b * cols + c] = s2;
 }
@@ -276,22 +328,25 @@ hipError_t launch_typed(const MomentumArgs& a, int axis, hipStream_t s) {
         else
             hipLaunchKernelGGL((momentum_rows<GT, true>), grid, dim3(kThreads), 0, s, a.ms, a.rows, a.cols, a.l1, a.sq);
     } else {
-        constexpr int64_t kWideCols = kThreads * 4;
-        const bool wide = a.cols % kWideCols == 0 && a.cols / kWideCols * a.nrb * a.batch >= 1024;
-        const int64_t per_block = wide ? kWideCols : 256;
-        dim3 grid((unsigned)((a.cols + per_block - 1) / per_block), (unsigned)a.nrb,
-                  (unsigned)a.batch);
-        auto launch = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, a.ms, a.rows, a.cols, a.rb_rows, a.nrb, a.part);
+        auto launch = [&](auto kernel, int threads, int64_t cols) {
+            const dim3 grid((unsigned)((a.cols + cols - 1) / cols), (unsigned)a.nrb, (unsigned)a.batch);
+            hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, a.ms, a.rows, a.cols, a.rb_rows, a.nrb, a.part);
         };
-        if (wide) launch(momentum_cols_partial<GT, true, false>);
-        else if (a.cols % 4) launch(momentum_cols_partial<GT, false, true>);
-        else launch(momentum_cols_partial<GT, false, false>);
+        if (a.cols % 4) launch(momentum_cols_partial<GT, true>, kThreads, 256);
+        else if (stream_waves(a.cols, a.nrb, a.batch) < kStreamWaves) launch(momentum_cols_partial<GT, false>, kThreads, 256);
+        else if (a.cols % (kThreads * 4) == 0) launch(momentum_cols_stream<GT>, kThreads, kThreads * 4);
+        else launch(momentum_cols_stream<GT>, 64, 256);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        dim3 grid2((unsigned)((a.cols + kFoldCols - 1) / kFoldCols), (unsigned)a.batch);
-        hipLaunchKernelGGL(momentum_cols_final, grid2, dim3(kThreads), 0, s, a.part, a.nrb,
-                           a.cols, a.l1, a.sq);
+        auto fold = [&](auto kernel, int ways) {
+            const int cols = kThreads / ways;
+            const dim3 grid((unsigned)((a.cols + cols - 1) / cols), (unsigned)a.batch);
+            hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, a.part, a.nrb, a.cols, a.l1, a.sq);
+        };
+        const int64_t blocks = (a.cols + kThreads - 1) / kThreads * a.batch;   // of one thread a column
+        if (blocks >= 1024) fold(momentum_cols_final<1>, 1);
+        else if (blocks >= 256) fold(momentum_cols_final<4>, 4);
+        else fold(momentum_cols_final<16>, 16);
     }
     return hipGetLastError();
 }

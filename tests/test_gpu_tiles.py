@@ -78,6 +78,9 @@ def test_split_k(hip_device, rows, cols, alpha, batch, kw, tol):
     (290, 2048, 1),     # columns by request on a wide matrix: a second block of 34 rows
     (4096, 1024, 64),   # wide blocks
     (4097, 1024, 65),   # wide blocks, a last block of one row
+    (520, 772, 300),    # single streaming waves, a last strip of one vector; a column folded by one thread
+    (1030, 1028, 52),   # the same just under their number; by four
+    (1030, 1028, 60),   # and just over
 ])
 @pytest.mark.parametrize("gdt", ["bf16", "f32"])
 def test_column_norm_blocks(hip_device, rows, cols, batch, gdt):
