@@ -112,15 +112,31 @@ __global__ __launch_bounds__(kThreads) void gather_rows(GatherArgs a) {
 // into the compact matrix. A block covers kCW columns x kRB rows; rank[c]
 // (selected columns below c) gives each selected column its line p, and
 // the block's lines are p0 = rank[c0] .. p1 = rank[c0 + kCW].
+//
+// Bound by memory, and by how evenly the blocks in flight mix reads and writes.
+// A block's ranks arrive before its rows are requested: rows requested beside
+// them are all waited for by the first use of a rank (16 x 8192 x 2048: 497 us,
+// 481 this way; with fp32 G 624 and 583 on one card). Blocks follow a row of M
+// from strip to strip. Where the last strip is a partial one and a matrix's
+// blocks are all in flight at once (kDownBlocks: two a compute unit), they go
+// down a strip instead, so that the shorter strips' blocks run together: 256 x
+// 2048 x 1408 1334 -> 1268 us, 64 x 4096 x 1000 548 -> 470; more blocks a matrix
+// lose by it (768, 20 x 8192 x 1500: 525 -> 533; 1032, 16 x 11008 x 1500: 562 ->
+// 616), and so do whole strips (64 x 3000 x 1536: 499 -> 517).
 constexpr int kCW = 256;
 constexpr int kRB = 64;
+constexpr int kDownBlocks = 512;
 
 template <typename GT, bool RAGGED, int THREADS>
 __global__ __launch_bounds__(THREADS) void update_cols(GatherArgs a) {
     __shared__ float tile[kCW][kRB + 1];   // [p - p0][r - r0]
     const int b = blockIdx.z;
-    const int64_t c0 = (int64_t)blockIdx.x * kCW;
-    const int r0 = blockIdx.y * kRB;
+    const int nx = gridDim.x, ny = gridDim.y;
+    const bool down = THREADS == kThreads && a.cols % kCW != 0 && nx * ny <= kDownBlocks;   // uniform
+    const int lin = blockIdx.x + nx * blockIdx.y;
+    const int64_t c0 = (int64_t)(down ? lin / ny : blockIdx.x) * kCW;
+    const int rb = down ? lin % ny : blockIdx.y;
+    const int r0 = rb * kRB;
     const int64_t cend = c0 + kCW < a.cols ? c0 + kCW : a.cols;
     const int32_t* __restrict__ rank = a.rank + (int64_t)b * (a.cols + 1);
     const int p0 = rank[c0], p1 = rank[cend];
@@ -139,6 +155,7 @@ __global__ __launch_bounds__(THREADS) void update_cols(GatherArgs a) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) pl[v] = (c + v < a.cols && rk[v + 1] > rk[v]) ? rk[v] - p0 : -1;
     }
+    asm volatile("" ::"v"(pl[0]), "v"(pl[1]), "v"(pl[2]), "v"(pl[3]));   // the ranks are here
     constexpr int kG = THREADS / 64;   // rows side by side
     constexpr int kR = kRB / kG;       // rows per thread
     {
@@ -183,7 +200,7 @@ __global__ __launch_bounds__(THREADS) void update_cols(GatherArgs a) {
     const bool last = cend == a.cols;   // this chunk also zeroes the padded lines k..kpad
     if (a.sq_part) {
         // sum of squares of this block's 64 rows of each selected column, in row order
-        double* sp = a.sq_part + ((int64_t)b * (a.opad / kRB) + blockIdx.y) * a.kpad + p0;
+        double* sp = a.sq_part + ((int64_t)b * (a.opad / kRB) + rb) * a.kpad + p0;
         for (int pi = threadIdx.x; pi < np; pi += THREADS) {
             double q = 0.0;
             for (int rl = 0; rl < kRB; ++rl) {

@@ -165,3 +165,24 @@ def test_row_norm_rests(hip_device, rows, cols, batches):
         binding.dion2_step_ex(Wn, Mn, Gn, 0.05, ns_steps=1, axis=AXIS_ROWS, dbg_norms=norms)
         torch.cuda.synchronize()
         assert bool((norms.cpu() == res["norms"][0]).all()) and bool((Mn == res["M"][0].to(hip_device)).all())
+
+
+@pytest.mark.parametrize("rows,cols,batch", [
+    (4097, 1000, 3),    # blocks down a strip, a last one of one row
+    (4097, 997, 3),     # the same with columns past the last vector
+    (8192, 1020, 2),    # as many blocks a matrix as that order takes
+    (8200, 1020, 2),    # more: along the rows
+    (8200, 2047, 1),
+    (2048, 1024, 6),    # whole strips: along the rows
+])
+@pytest.mark.parametrize("rand", [None, (3, 1, 0)], ids=["l1", "random"])
+def test_column_update_orders(hip_device, rows, cols, batch, rand):
+    """The column update's two block orders: M, K, W given O, the norms of the
+    single pass, and every matrix of a batch alike."""
+    W, M, G = workloads.make_group(one_group_workload(rows, cols, axis=AXIS_COLS, name=f"upd{rows}x{cols}"), 0, hip_device)
+    Wn, Mn, Gn = (t.repeat(batch, 1, 1) for t in (W, M, G))
+    res = run_gpu(Wn, Mn, Gn, 0.02, axis=AXIS_COLS, ns_steps=1, rand=rand, norms=rand is None)
+    for b in sorted({0, batch - 1}):
+        check_matrix(res, b, 0.02, ns_steps=1, axis=AXIS_COLS, rand=rand)
+    if rand is None:
+        assert bool((res["M"] == res["M"][0]).all()) and bool((res["W"] == res["W"][0]).all())
