@@ -309,7 +309,7 @@ __global__ __launch_bounds__(kThreads) void apply_cols_strip(ApplyArgs a) {
 // K[p], value O^T[r][p], read coalesced), and the row goes back to W whole.
 // Every lane does the same number of updates, so nothing diverges; K is
 // staged in LDS once per block. A row whose length is not a multiple of 8
-// (`ragged`) ends in part of a chunk. The first 64 KT ranks of a row are fetched
+// (RAGGED) ends in part of a chunk. The first 64 KT ranks of a row are fetched
 // with the row (one row ahead); larger k take further passes of 64 KT.
 // Rows per block: 32 (8 a wave) where that gives two blocks a compute unit;
 // a launch of fewer halves them down to one row a wave, since a wave's rows
@@ -318,7 +318,7 @@ __global__ __launch_bounds__(kThreads) void apply_cols_strip(ApplyArgs a) {
 constexpr int kSelRowBytes = 8192;           // LDS row buffer per wave
 constexpr int kSelMaxK = 4096;               // k <= cols <= 4096 (bf16) or 2048 (fp32)
 
-template <typename WT, int NCH, int KT>
+template <typename WT, int NCH, int KT, bool RAGGED>
 __global__ __launch_bounds__(kThreads) void apply_cols_sel(ApplyArgs a, int block_rows) {
     __shared__ __attribute__((aligned(16))) WT row_s[4][kSelRowBytes / sizeof(WT)];
     extern __shared__ int32_t sel_s[];   // k entries (dynamic: k * 4 bytes)
@@ -353,7 +353,6 @@ __global__ __launch_bounds__(kThreads) void apply_cols_sel(ApplyArgs a, int bloc
         cval[j] = c < a.cols;
         coff[j] = cval[j] ? c : (int)a.cols - kLaneCols;
     }
-    const bool ragged = a.cols % kLaneCols != 0;   // uniform
     auto left = [&](int j) { return (int)a.cols - kLaneCols * (lane + 64 * j); };   // columns from a chunk's first
     // Software pipelined over the wave's rows: the loads of the next row are
     // issued before the stores of this one. Vector memory counters retire in
@@ -361,7 +360,7 @@ __global__ __launch_bounds__(kThreads) void apply_cols_sel(ApplyArgs a, int bloc
     // wait for those stores to be acknowledged; issued before them, it does
     // not. The last row's "next" loads re-read that row, unused.
     auto load_row = [&](int64_t r, Chunk8<WT> (&w)[NCH], float (&o)[KT]) {
-        if (!ragged) {
+        if constexpr (!RAGGED) {
 #pragma unroll
             for (int j = 0; j < NCH; ++j) w[j].load(W + r * a.cols + coff[j]);
         } else {
@@ -414,7 +413,7 @@ __global__ __launch_bounds__(kThreads) void apply_cols_sel(ApplyArgs a, int bloc
         for (int j = 0; j < NCH; ++j) {
             if (cval[j]) {
                 w[j].get_lds(rs + coff[j]);
-                if (!ragged) w[j].store(W + r * a.cols + coff[j]);
+                if constexpr (!RAGGED) w[j].store(W + r * a.cols + coff[j]);
                 else w[j].store_part(W + r * a.cols + coff[j], left(j));
             }
         }
@@ -432,9 +431,12 @@ void launch_cols_sel_k(const ApplyArgs& a, hipStream_t s) {
     while (block_rows > 4 && (a.rows + block_rows - 1) / block_rows * a.batch < 512) block_rows /= 2;
     dim3 grid((unsigned)((a.rows + block_rows - 1) / block_rows), (unsigned)a.batch);
     const size_t lds = (size_t)a.k * sizeof(int32_t);   // K's copy; the row buffers are static
-    if (a.k <= 256) hipLaunchKernelGGL((apply_cols_sel<WT, NCH, 4>), grid, dim3(kThreads), lds, s, a, block_rows);
-    else if (a.k <= 512) hipLaunchKernelGGL((apply_cols_sel<WT, NCH, 8>), grid, dim3(kThreads), lds, s, a, block_rows);
-    else hipLaunchKernelGGL((apply_cols_sel<WT, NCH, 16>), grid, dim3(kThreads), lds, s, a, block_rows);
+    auto launch = [&](auto even, auto ragged) {
+        hipLaunchKernelGGL(a.cols % kLaneCols ? ragged : even, grid, dim3(kThreads), lds, s, a, block_rows);
+    };
+    if (a.k <= 256) launch(apply_cols_sel<WT, NCH, 4, false>, apply_cols_sel<WT, NCH, 4, true>);
+    else if (a.k <= 512) launch(apply_cols_sel<WT, NCH, 8, false>, apply_cols_sel<WT, NCH, 8, true>);
+    else launch(apply_cols_sel<WT, NCH, 16, false>, apply_cols_sel<WT, NCH, 16, true>);
 }
 
 template <typename WT>
