@@ -155,7 +155,7 @@ __global__ __launch_bounds__(THREADS) void update_cols(GatherArgs a) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) pl[v] = (c + v < a.cols && rk[v + 1] > rk[v]) ? rk[v] - p0 : -1;
     }
-    asm volatile("" ::"v"(pl[0]), "v"(pl[1]), "v"(pl[2]), "v"(pl[3]));   // the ranks are here
+    if constexpr (THREADS == kThreads) asm volatile("" ::"v"(pl[0]), "v"(pl[1]), "v"(pl[2]), "v"(pl[3]));   // the ranks are here
     constexpr int kG = THREADS / 64;   // rows side by side
     constexpr int kR = kRB / kG;       // rows per thread
     {
