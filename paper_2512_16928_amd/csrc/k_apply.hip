@@ -16,6 +16,7 @@
 //                     strips, the strip's slice of O^T staged in LDS, only
 //                     chunks with a selected column rewritten;
 //   apply_cols        other column counts: four columns per lane.
+#include <type_traits>
 
 #include "dion2_device.h"
 
@@ -309,7 +310,7 @@ __global__ __launch_bounds__(kThreads) void apply_cols_strip(ApplyArgs a) {
 // K[p], value O^T[r][p], read coalesced), and the row goes back to W whole.
 // Every lane does the same number of updates, so nothing diverges; K is
 // staged in LDS once per block. A row whose length is not a multiple of 8
-// (RAGGED) ends in part of a chunk. The first 64 KT ranks of a row are fetched
+// (RAGGED: perhaps) ends in part of a chunk. The first 64 KT ranks of a row are fetched
 // with the row (one row ahead); larger k take further passes of 64 KT.
 // Rows per block: 32 (8 a wave) where that gives two blocks a compute unit;
 // a launch of fewer halves them down to one row a wave, since a wave's rows
@@ -353,6 +354,7 @@ __global__ __launch_bounds__(kThreads) void apply_cols_sel(ApplyArgs a, int bloc
         cval[j] = c < a.cols;
         coff[j] = cval[j] ? c : (int)a.cols - kLaneCols;
     }
+    const bool ragged = RAGGED && a.cols % kLaneCols != 0;   // uniform
     auto left = [&](int j) { return (int)a.cols - kLaneCols * (lane + 64 * j); };   // columns from a chunk's first
     // Software pipelined over the wave's rows: the loads of the next row are
     // issued before the stores of this one. Vector memory counters retire in
@@ -360,7 +362,7 @@ __global__ __launch_bounds__(kThreads) void apply_cols_sel(ApplyArgs a, int bloc
     // wait for those stores to be acknowledged; issued before them, it does
     // not. The last row's "next" loads re-read that row, unused.
     auto load_row = [&](int64_t r, Chunk8<WT> (&w)[NCH], float (&o)[KT]) {
-        if constexpr (!RAGGED) {
+        if (!ragged) {
 #pragma unroll
             for (int j = 0; j < NCH; ++j) w[j].load(W + r * a.cols + coff[j]);
         } else {
@@ -413,7 +415,7 @@ __global__ __launch_bounds__(kThreads) void apply_cols_sel(ApplyArgs a, int bloc
         for (int j = 0; j < NCH; ++j) {
             if (cval[j]) {
                 w[j].get_lds(rs + coff[j]);
-                if constexpr (!RAGGED) w[j].store(W + r * a.cols + coff[j]);
+                if (!ragged) w[j].store(W + r * a.cols + coff[j]);
                 else w[j].store_part(W + r * a.cols + coff[j], left(j));
             }
         }
@@ -431,12 +433,22 @@ void launch_cols_sel_k(const ApplyArgs& a, hipStream_t s) {
     while (block_rows > 4 && (a.rows + block_rows - 1) / block_rows * a.batch < 512) block_rows /= 2;
     dim3 grid((unsigned)((a.rows + block_rows - 1) / block_rows), (unsigned)a.batch);
     const size_t lds = (size_t)a.k * sizeof(int32_t);   // K's copy; the row buffers are static
-    auto launch = [&](auto even, auto ragged) {
-        hipLaunchKernelGGL(a.cols % kLaneCols ? ragged : even, grid, dim3(kThreads), lds, s, a, block_rows);
+    auto launch = [&](auto kt) {
+        constexpr int KT = decltype(kt)::value;
+        auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kThreads), lds, s, a, block_rows); };
+        // bf16 rows of whole chunks have a kernel of their own, without the scalar
+        // registers that both kinds of access spill (64 x 4096 x 512: 112 -> 107
+        // us). fp32 ones do not: the compiler then orders a row's loads
+        // otherwise, and that measured slower (64 x 4096 x 1024 at k = 512: 747
+        // us against 672; with the two loads of a chunk kept in order 724)
+        if constexpr (sizeof(WT) == 2) {
+            if (a.cols % kLaneCols == 0) return run(apply_cols_sel<WT, NCH, KT, false>);
+        }
+        run(apply_cols_sel<WT, NCH, KT, true>);
     };
-    if (a.k <= 256) launch(apply_cols_sel<WT, NCH, 4, false>, apply_cols_sel<WT, NCH, 4, true>);
-    else if (a.k <= 512) launch(apply_cols_sel<WT, NCH, 8, false>, apply_cols_sel<WT, NCH, 8, true>);
-    else launch(apply_cols_sel<WT, NCH, 16, false>, apply_cols_sel<WT, NCH, 16, true>);
+    if (a.k <= 256) launch(std::integral_constant<int, 4>{});
+    else if (a.k <= 512) launch(std::integral_constant<int, 8>{});
+    else launch(std::integral_constant<int, 16>{});
 }
 
 template <typename WT>
