@@ -1197,9 +1197,10 @@ hipError_t sym_three(const GemmArgs& a, const SymPlan& p, hipStream_t s) {
             // 384, 64: 24.8 against 23.1); polynomial ones spill in the other
             // loop within the registers of two blocks a CU (s = 512, 64: 55.4
             // against 57.2)
-            if (EPI != EPI_SPLIT || a.K >= 1024)
-                return launch_sym<3, EPI, Tile<3, 0, 128, 128, kSliceK, 4, 2, 2, false, true>>(a, 1, s);
-            return launch_sym<3, EPI, Tile<3, 0, 128, 128, kSliceK, 4, 2, 2>>(a, 1, s);
+            if constexpr (EPI == EPI_SPLIT) {
+                if (a.K < 1024) return launch_sym<3, EPI, Tile<3, 0, 128, 128, kSliceK, 4, 2, 2>>(a, 1, s);
+            }
+            return launch_sym<3, EPI, Tile<3, 0, 128, 128, kSliceK, 4, 2, 2, false, true>>(a, 1, s);
     }
 }
 
