@@ -1101,17 +1101,18 @@ SymPlan plan_sym(const GemmArgs& a, GemmEpi epi, int npass) {
     const int64_t n64 = sym_tiles(a, mr, 64), n128 = sym_tiles(a, a.M, 128);
     const int64_t n256 = a.M % 256 ? 0 : sym_tiles(a, a.M, 256);
     if (npass == 3) {
-        // one block a compute unit: four stages; beyond, two or three of the
-        // two-stage ring's share one, as long as they are few: up to 512 (495
-        // at s = 640: 20.8 against 22.3 us; 408 at s = 1024: 20.0 against 27.7;
-        // 544 there 25.2 against 24.6), 560 where K is at most 512 (640 at s =
-        // 256: 13.6 against 11.4; 576 at s = 512: 15.2 against 15.6 alone, but
-        // the grouped call of the 1B stack, whose other groups use the same
-        // caches, 0.6% slower), and on a single 128 x 128 tile, of which they
-        // are three quarters, up to 1600 (384 at s = 128: 5.8 against 7.5 us;
-        // 1536: 15.1 against 17.0)
+        // one block a compute unit: four stages; beyond, two of the two-stage
+        // ring's share one (us on 64 x 64 and on 128 x 128: 510 at s = 320 17.5
+        // and 19.4, 495 at s = 640 24.6 and 25.3, 408 at s = 1024 21.8 and 30.3;
+        // 540 at s = 320 20.0 and 17.7, 550 at s = 640 30.9 and 26.5). A number
+        // that gemm renumbers onto the XCDs keeps a matrix in one L2, and up to
+        // K = 512 holds to 640 (600 at s = 320 14.1 and 17.4, 640 at s = 256 12.5
+        // and 14.6, 576 at s = 512 17.6 and 18.1; 672 at s = 384 17.0 and 16.2,
+        // 720 at s = 512 20.1 and 19.8; 544 at s = 1024 29.4 and 28.7). On a
+        // single 128 x 128 tile, of which they are three quarters, up to 1600
+        // (384 at s = 128: 5.8 against 7.5 us; 1536: 15.1 against 17.0)
         if (n64 <= 256) return {SYM_64, split && a.K >= 1024 ? parts_of(a, n64, 64, mr, 256, 512) : 1};
-        if (n64 <= (mr <= 128 ? 1600 : a.K <= 512 ? 560 : 512)) return {SYM_64S2, 1};
+        if (n64 <= (mr <= 128 ? 1600 : a.K <= 512 && n64 % kXcds == 0 ? 640 : 512)) return {SYM_64S2, 1};
         // two rounds of 256 x 256 tiles for the plain products (the
         // polynomial epilogues spill on them): 5-10% at s = 1024 and 2048
         const bool poly = epi == EPI_POLY || epi == EPI_QPOLY;

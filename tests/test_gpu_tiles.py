@@ -23,10 +23,28 @@ def nan_workspace(batch, rows, cols, alpha, device, **kw):
     return torch.full((n,), 0xFF, dtype=torch.uint8, device=device)
 
 
+def gram_launches(call):
+    """Kernels that the call's Gram products take: two each where K is split."""
+    binding.dion2_profile_reset()
+    binding.dion2_profile_enable(True)
+    call()
+    torch.cuda.synchronize()
+    prof = binding.dion2_profile_read()
+    binding.dion2_profile_enable(False)
+    return prof["ns_gram"]["launches"]
+
+
+def gram_products(batch, rows, cols, alpha, **kw):
+    """How many Gram products a call of five steps has: one per step in the DIRECT form."""
+    kw.pop("select_rule", None)
+    return 5 if binding.dion2_plan_form(batch, rows, cols, alpha, **kw)[0] == NS_DIRECT else 1
+
+
 @pytest.mark.parametrize("rows,cols,alpha,batches,kw", [
     (260, 1030, 0.25, (1, 2, 90), {}),                           # s = 65: one 64-tile more than s fills
     (1030, 516, 0.5, (1, 17, 18, 38), dict(ns_form=NS_GRAM)),    # s = 258, columns: 15 tiles each, 255 to 570 blocks
     (1000, 1000, 0.25, (1, 25, 26, 56, 57), dict(ns_form=NS_GRAM)),   # s = 250: 250, 260, 560 and 570 blocks
+    (1000, 1000, 0.25, (1, 51, 52, 54, 64, 72), dict(ns_form=NS_GRAM)),   # 510 to 720, of which 520, 640 and 720 by XCD
     (640, 1000, 0.5, (1, 12, 17), dict(ns_form=NS_DIRECT)),      # s = 320: one-pass products at 252 and 357 blocks
     (450, 700, 1.0, (1, 8, 13), {}),                             # s = 450, DIRECT, 448 sides written of 512
     (960, 960, 0.25, (1, 26, 57), dict(ns_master=MASTER_FP32)),   # K = 960: the three-pass Gram splits from 1024
@@ -38,8 +56,8 @@ def test_tiles_bitwise_across_batches(hip_device, rows, cols, alpha, batches, kw
     for n in batches:
         Wn, Mn, Gn = (t.repeat(n, 1, 1) for t in (W, M, G))
         ws = nan_workspace(n, rows, cols, alpha, hip_device, **kw)
-        binding.dion2_step_ex(Wn, Mn, Gn, alpha, workspace=ws, **kw)
-        torch.cuda.synchronize()
+        launches = gram_launches(lambda: binding.dion2_step_ex(Wn, Mn, Gn, alpha, workspace=ws, **kw))
+        assert launches == gram_products(n, rows, cols, alpha, **kw), f"batch {n}: K split"
         got = Wn.view(torch.int16)
         if first is None:
             first = got[0].clone()
@@ -67,8 +85,8 @@ def test_split_k(hip_device, rows, cols, alpha, batch, kw, tol):
     for b in (0, batch - 1):
         check_matrix(res, b, alpha, ns_tol=tol, rand=run.get("rand"))
     ws = nan_workspace(batch, rows, cols, alpha, hip_device, **kw)
-    binding.dion2_step_ex(W2, M2, G, alpha, workspace=ws, **kw)
-    torch.cuda.synchronize()
+    launches = gram_launches(lambda: binding.dion2_step_ex(W2, M2, G, alpha, workspace=ws, **kw))
+    assert launches == 2 * gram_products(batch, rows, cols, alpha, **kw), "K not split"
     assert torch.equal(W2.cpu().view(torch.int16), res["W"].view(torch.int16)) and torch.equal(M2.cpu(), res["M"])
 
 
@@ -125,15 +143,6 @@ def test_split_k_in_grouped_calls(hip_device, shapes, kw):
     wl = workloads.Workload("gsplit", "test", tuple(workloads.Group(f"g{i}", *s) for i, s in enumerate(shapes)), (0.25,))
     stacks = [workloads.make_group(wl, i, hip_device) for i in range(len(shapes))]
     solo = [tuple(t.clone() for t in st) for st in stacks]
-
-    def gram_launches(call):
-        binding.dion2_profile_reset()
-        binding.dion2_profile_enable(True)
-        call()
-        torch.cuda.synchronize()
-        prof = binding.dion2_profile_read()
-        binding.dion2_profile_enable(False)
-        return prof["ns_gram"]["launches"]
 
     for W, M, G in solo:
         want = 2 if W.shape[-1] != 1100 else 1
