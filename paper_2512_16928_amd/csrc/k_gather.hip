@@ -12,6 +12,8 @@
 // (line p, other index j): the side that is contiguous in M is read and
 // written directly, the other side goes through an LDS tile. Tiles cover the
 // padded extents, and padding (p >= k or j >= d_oth) is written as zero.
+#include <utility>
+
 #include "dion2_device.h"
 
 namespace dion2 {
@@ -114,9 +116,11 @@ __global__ __launch_bounds__(kThreads) void gather_rows(GatherArgs a) {
 // the block's lines are p0 = rank[c0] .. p1 = rank[c0 + kCW].
 //
 // Bound by memory, and by how evenly the blocks in flight mix reads and writes.
-// A block's ranks arrive before its rows are requested: rows requested beside
-// them are all waited for by the first use of a rank (16 x 8192 x 2048: 497 us,
-// 481 this way; with fp32 G 624 and 583 on one card). Blocks follow a row of M
+// In launches of whole strips a block's ranks arrive before its rows are
+// requested: rows requested beside them are all waited for by the first use of a
+// rank (16 x 8192 x 2048: 497 us, 481 this way; with fp32 G 624 and 583 on one
+// card; partial strips gain nothing, and small launches are bound by latency:
+// 8192 x 2048 40.7 and 42). Blocks follow a row of M
 // from strip to strip. Where the last strip is a partial one and a matrix's
 // blocks are all in flight at once (kDownBlocks: two a compute unit), they go
 // down a strip instead, so that the shorter strips' blocks run together: 256 x
@@ -128,14 +132,12 @@ constexpr int kRB = 64;
 constexpr int kDownBlocks = 512;
 
 template <typename GT, bool RAGGED, int THREADS>
-__global__ __launch_bounds__(THREADS) void update_cols(GatherArgs a) {
+__global__ __launch_bounds__(THREADS) void update_cols(GatherArgs a, int down) {
     __shared__ float tile[kCW][kRB + 1];   // [p - p0][r - r0]
     const int b = blockIdx.z;
-    const int nx = gridDim.x, ny = gridDim.y;
-    const bool down = THREADS == kThreads && a.cols % kCW != 0 && nx * ny <= kDownBlocks;   // uniform
-    const int lin = blockIdx.x + nx * blockIdx.y;
-    const int64_t c0 = (int64_t)(down ? lin / ny : blockIdx.x) * kCW;
-    const int rb = down ? lin % ny : blockIdx.y;
+    const bool ranks_first = THREADS == kThreads && a.cols % kCW == 0;   // uniform
+    const int64_t c0 = (int64_t)(down ? blockIdx.y : blockIdx.x) * kCW;
+    const int rb = down ? blockIdx.x : blockIdx.y;
     const int r0 = rb * kRB;
     const int64_t cend = c0 + kCW < a.cols ? c0 + kCW : a.cols;
     const int32_t* __restrict__ rank = a.rank + (int64_t)b * (a.cols + 1);
@@ -155,7 +157,7 @@ __global__ __launch_bounds__(THREADS) void update_cols(GatherArgs a) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) pl[v] = (c + v < a.cols && rk[v + 1] > rk[v]) ? rk[v] - p0 : -1;
     }
-    if constexpr (THREADS == kThreads) asm volatile("" ::"v"(pl[0]), "v"(pl[1]), "v"(pl[2]), "v"(pl[3]));   // the ranks are here
+    if (ranks_first) asm volatile("" ::"v"(pl[0]), "v"(pl[1]), "v"(pl[2]), "v"(pl[3]));   // the ranks are here
     constexpr int kG = THREADS / 64;   // rows side by side
     constexpr int kR = kRB / kG;       // rows per thread
     {
@@ -423,7 +425,9 @@ hipError_t launch_gather(const GatherArgs& a, int axis, int g_bf16, hipStream_t 
         // same bytes a unit, and four times the waves to place the columns
         // (2 x 1024 x 472: 11.8 us on four waves, 8.6 on sixteen).
         const bool small = (int64_t)grid.x * grid.y * grid.z <= 512;
-        auto launch = [&](auto kernel, int threads) { hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, a); };
+        const bool down = !small && a.cols % kCW != 0 && grid.x * grid.y <= kDownBlocks;
+        if (down) std::swap(grid.x, grid.y);
+        auto launch = [&](auto kernel, int threads) { hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, a, (int)down); };
         auto sized = [&](auto narrow, auto wide) { small ? launch(wide, 1024) : launch(narrow, kThreads); };
         if (g_bf16 && a.cols % 4) sized(update_cols<uint16_t, true, kThreads>, update_cols<uint16_t, true, 1024>);
         else if (g_bf16) sized(update_cols<uint16_t, false, kThreads>, update_cols<uint16_t, false, 1024>);
