@@ -56,7 +56,9 @@ constexpr int64_t kRowChunk = 64 * 4 * kRowVecs;   // entries of a row a wave ta
 // in a launch that the 256 MB last-level cache about holds (200 x 256 x 256: the
 // step 77 and 83; 1000 x 256 x 256 331 and 327). BATCHED wins on rows between,
 // where one vector at a time is a chain of up to eight waits (64 x 1000 x 2000
-// 234 and 211, 1 x 1000 x 2000 11 and 8.5).
+// 234 and 211, 1 x 1000 x 2000 11 and 8.5), and with fp32 G behind whole chunks
+// in launches of less than a wave a SIMD (1 x 512 x 4000 12.3 and 10.8; with
+// bf16 G 12.4 and 13.1).
 template <typename GT, bool BATCHED>
 __global__ __launch_bounds__(kThreads) void momentum_rows(MatSet ms, int64_t rows, int64_t cols,
                                                           double* __restrict__ l1,
@@ -323,7 +325,7 @@ hipError_t launch_typed(const MomentumArgs& a, int axis, hipStream_t s) {
         const int64_t lines = a.rows * a.batch;
         const bool cached = a.cols >= kRowChunk ? lines * (a.cols % kRowChunk) <= int64_t(1) << 27
                                                 : a.cols <= 512 && lines * a.cols <= int64_t(1) << 25;
-        if (a.cols % 4 == 0 && cached)
+        if (a.cols % 4 == 0 && cached && (sizeof(GT) == 2 || a.cols < kRowChunk || lines >= 1024))
             hipLaunchKernelGGL((momentum_rows<GT, false>), grid, dim3(kThreads), 0, s, a.ms, a.rows, a.cols, a.l1, a.sq);
         else
             hipLaunchKernelGGL((momentum_rows<GT, true>), grid, dim3(kThreads), 0, s, a.ms, a.rows, a.cols, a.l1, a.sq);
