@@ -18,8 +18,9 @@
  *   - M is fp32; the accumulate and the decay are single IEEE fp32 RNE
  *     operations (bitwise reproducible).
  *   - The l1 norm of each line is accumulated in double-double from the fp32
- *     values of M and rounded once to fp64, in an order fixed by the shape,
- *     so selection does not depend on scheduling. It equals the exact sum of
+ *     values of M and rounded once to fp64, in an order fixed by the shape
+ *     and the number of matrices in the call (or in the group, in a grouped
+ *     call), so selection does not depend on scheduling. It equals the exact sum of
  *     |M_ij| rounded once to fp64, except when that exact sum S lies within
  *     about n^2 2^-106 S (n the line's length) of a point halfway between
  *     two adjacent fp64 values: there the low word's own rounding can move
@@ -52,6 +53,12 @@
  *     a bf16 hi/lo pair (about 16 significant bits) instead of being rounded
  *     once to bf16: the Gram matrix and the final product take three passes,
  *     and the iteration runs in the GRAM order.
+ *     Every sum is taken in an order fixed by the shape, the options and the
+ *     number of matrices in the call or group: a Gram product over a long
+ *     side is cut into parts by how many matrices there are, so the same
+ *     matrix can differ in its last bits between calls of different batch
+ *     sizes, and never between runs or between a grouped call and the same
+ *     group's own call.
  *     Default coefficients are Muon's quintic (3.4445, -4.7750, 2.0315) at
  *     every step, eps = 1e-7.
  *   - The weight update is computed in fp64 from the fp32 O and rounded once
@@ -334,8 +341,8 @@ typedef struct dion2_group {
 /* The step of Algorithm 1 for several same-shape groups in one call on one
    stream, with shared hyper-parameters and options (a model's whole layer
    stack, say; every matrix is stepped independently, as Algorithm 1 is per
-   matrix, with the options' meaning as in dion2_step_ex). The result is bitwise that of dion2_step_ex called for each
-   group in order; for the RANDOM rule group g's matrix indices start at
+   matrix, with the options' meaning as in dion2_step_ex). The result is
+   bitwise that of dion2_step_ex called for each group in order; for the RANDOM rule group g's matrix indices start at
    rand_matrix0 plus the batches of groups 0 .. g-1. Groups whose
    Newton-Schulz runs in the GRAM form with the same padded s x s size share
    one batched chain of s x s products, launched once for all of them.

@@ -119,12 +119,14 @@ int make_plan(int batch, int64_t rows, int64_t cols, float alpha, int axis, int 
     P.z_is_L = P.k <= P.d_oth;
     P.s_pad = P.z_is_L ? P.kpad : P.opad;
     P.l_pad = P.z_is_L ? P.opad : P.kpad;
-    // Every s x s matrix of either form is block diagonal, the s x s block
-    // and the padding (Z's padding rows are zero; only Q's a I reaches the
-    // padding's diagonal), so a product whose inner dimension is s or l
-    // sums only to the real side, rounded up to the 32-deep K slice: the
-    // terms left out are exact zeros in every real entry. (MoE experts:
-    // s = 352 padded to 384, one slice in twelve.)
+    // Every s x s matrix of either form is block diagonal as far as it is
+    // written, the s x s block and the padding (Z's padding rows are zero; only
+    // Q's a I reaches the padding's diagonal), so a product whose inner dimension
+    // is s or l sums only to the real side, rounded up to the 32-deep K slice
+    // (64-deep in some tiles): the terms left out are exact zeros in every real
+    // entry. Past the next multiple of 64 small tiles leave s x s matrices
+    // unwritten, so no sum may run on to s_pad. (MoE experts: s = 352 padded to
+    // 384, one slice in twelve.)
     P.s_k = round_up(P.z_is_L ? P.k : P.d_oth, kSliceK);
     P.l_k = round_up(P.z_is_L ? P.d_oth : P.k, kSliceK);
     // With a compact matrix of one tile a side the DIRECT form's bf16

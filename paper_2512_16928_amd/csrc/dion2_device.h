@@ -8,8 +8,12 @@
 //                           scaled by 1 / (||M[K]||_F + eps), zero padding.
 //   Its transpose     LT : [opad][kpad] bf16. Newton-Schulz iterates on the
 //                           wide one of the two (L when k <= d_oth).
-//   kpad, opad are k and d_oth rounded up to the GEMM tile (128); every
-//   padded entry is zero, which the Newton-Schulz polynomial keeps at zero.
+//   kpad, opad are k and d_oth rounded up to the GEMM tile (128). The
+//   compact matrix is gathered with zeros in all its padding. Along s, the
+//   shorter side, the Newton-Schulz products keep entries zero only up to the
+//   next multiple of 64 (Q and P: zero off the diagonal there); what lies past
+//   it may never be written and may hold anything, NaN included. So no sum
+//   over s runs past that multiple, and rows past it only make rows past it.
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -47,8 +47,11 @@
 // block then leaves in whole row segments (64 bytes of bf16 or 128 bytes of
 // fp32 per row), row-major or transposed for the mirrored copy.
 //
-// All dimensions are multiples of the tile (compact buffers are zero padded
-// to 128, and the padding stays zero through every step).
+// All dimensions are multiples of the tile: buffers are padded to 128. An s x s
+// matrix (and X along s) is defined, zeros past s, up to the next multiple of
+// 64 (of a shared chain's widest member); past it 64-row tiles leave it
+// unwritten, so a tile choice may read rows there, which give rows there, but
+// no K extent may reach it.
 #include <algorithm>
 #include <type_traits>
 
@@ -1057,9 +1060,10 @@ hipError_t launch_split(const GemmArgs& a, hipStream_t s) {
 
 // ---- tile and split choices
 //
-// 256 compute units take two blocks of any of these tiles at once (one of a
-// 256 x 256 tile), so a launch of few tiles leaves most of the chip idle and
-// costs one block's serial time: the slice loop's latency and a big tile's
+// 256 compute units take two blocks of most of these tiles at once (one of a
+// 256 x 256 or 256 x 128 tile, or of a three-pass 64 x 128 one, whose rings
+// take 96 KB of LDS or more), so a launch of few tiles leaves most of the chip
+// idle and costs one block's serial time: the slice loop's latency and a big tile's
 // epilogue. There the tile shrinks to 64 x 64 (four times the blocks, each
 // with four slices in flight), and a long K is split over more blocks, whose
 // fp32 partials a second launch folds in order. A larger launch is bound by

@@ -10,13 +10,15 @@
 // Row mode: one wave per row (four rows per 256-thread block); every lane
 // streams 4-element vectors (16 B of M, 8 B of bf16 G), eight vectors in
 // flight, and the wave reduces in a fixed shuffle order. M and G are
-// streamed with non-temporal loads and stores (each is touched once).
+// streamed with non-temporal loads and stores (each is touched once), but for
+// the ends of long rows and short rows in some launches (momentum_rows).
 // Column mode: M is only read here (the gather pass rewrites whole rows of
 // M once the selection is known, so the sum is stored once); each thread
 // owns 4 adjacent columns of a block of rows and writes double-double
-// partials, and a second pass folds the row blocks in order. No
-// floating-point atomics anywhere: results are run-to-run bitwise
-// reproducible.
+// partials, and a second pass folds the row blocks in order. The row blocks
+// and the fold depend on the matrices' shape and number, so the last bits of
+// the squared norms do too. No floating-point atomics anywhere: results are
+// run-to-run bitwise reproducible.
 #include "dion2_device.h"
 
 namespace dion2 {

@@ -772,7 +772,7 @@ def test_compact_x_lo_halves_fp32_master(hip_device, rows, cols, alpha, axis):
 
 @pytest.mark.parametrize("rows,cols,axis", [
     (1 << 20, 64, AXIS_AUTO),     # columns of a million entries: Gram over K = 2^20
-    (1 << 20, 16, AXIS_ROWS),     # 2^20 lines to select from (keys beyond the LDS cache), L^T
+    (1 << 20, 16, AXIS_ROWS),     # 2^20 lines to select from (keys read again in every pass), L^T
     (16, 1 << 20, AXIS_AUTO),     # rows of a million entries: 8192 column tiles, fused update
 ])
 def test_maximum_dimension(hip_device, rows, cols, axis):

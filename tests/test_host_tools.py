@@ -37,6 +37,10 @@ def test_phase_of_kernel_names():
         "void dion2::(anonymous namespace)::gemm<2, 10, dion2::(anonymous namespace)::Tile<2, 1, 128, 128, 32, 4, 2, 2, false, false>, false>(dion2::GemmArgs)": "ns_update",
         "void dion2::(anonymous namespace)::chain_small<64>(dion2::SmallChainArgs)": "ns_poly",
         "void dion2::(anonymous namespace)::select_reg<1024, 2>(dion2::SelectArgs)": "select",
+        "void dion2::(anonymous namespace)::momentum_cols_stream<unsigned short>(dion2::MatSet, long, long, int, int, double*)": "momentum",
+        "void dion2::(anonymous namespace)::momentum_cols_final<4>(double const*, int, long, double*, double*)": "momentum",
+        "void dion2::(anonymous namespace)::update_cols<unsigned short, false, 256>(dion2::GatherArgs, int)": "gather",
+        "void dion2::(anonymous namespace)::apply_cols_sel<unsigned short, 4, 8, false>(dion2::ApplyArgs, int)": "apply",
         "dion2::transpose_bf16(unsigned short const*, unsigned short*, long, long, long)": "ns_update",
         "dion2::(anonymous namespace)::colpass_compact(dion2::ColpassArgs)": "gather",
         "dion2::(anonymous namespace)::colpass_fold(dion2::ColpassArgs)": "gather",
