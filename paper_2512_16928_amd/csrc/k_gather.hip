@@ -118,15 +118,16 @@ __global__ __launch_bounds__(kThreads) void gather_rows(GatherArgs a) {
 // Bound by memory, and by how evenly the blocks in flight mix reads and writes.
 // In launches of whole strips a block's ranks arrive before its rows are
 // requested: rows requested beside them are all waited for by the first use of a
-// rank (16 x 8192 x 2048: 497 us, 481 this way; with fp32 G 624 and 583 on one
-// card; partial strips gain nothing, and small launches are bound by latency:
-// 8192 x 2048 40.7 and 42). Blocks follow a row of M
-// from strip to strip. Where the last strip is a partial one and a matrix's
-// blocks are all in flight at once (kDownBlocks: two a compute unit), they go
-// down a strip instead, so that the shorter strips' blocks run together: 256 x
-// 2048 x 1408 1334 -> 1268 us, 64 x 4096 x 1000 548 -> 470; more blocks a matrix
-// lose by it (768, 20 x 8192 x 1500: 525 -> 533; 1032, 16 x 11008 x 1500: 562 ->
-// 616), and so do whole strips (64 x 3000 x 1536: 499 -> 517).
+// rank (16 x 8192 x 2048: 497 us, 481 this way; with fp32 G 624 and 583).
+// Partial strips gain nothing by it, and small launches are bound by latency
+// (8192 x 2048: 40.7 us, 42 this way).
+// Blocks follow a row of M from strip to strip. Where the last strip is a
+// partial one and a matrix's blocks are all in flight at once (kDownBlocks: two
+// a compute unit), they go down a strip instead, so that the shorter strip's
+// blocks run together: 256 x 2048 x 1408 1334 -> 1268 us, 64 x 4096 x 1000 548
+// -> 470. More blocks a matrix lose by it (768, 20 x 8192 x 1500: 525 -> 533;
+// 1032, 16 x 11008 x 1500: 562 -> 616), and so do whole strips (64 x 3000 x
+// 1536: 499 -> 517).
 constexpr int kCW = 256;
 constexpr int kRB = 64;
 constexpr int kDownBlocks = 512;

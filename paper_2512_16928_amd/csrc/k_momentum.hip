@@ -337,7 +337,8 @@ hipError_t launch_typed(const MomentumArgs& a, int axis, hipStream_t s) {
             hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, a.ms, a.rows, a.cols, a.rb_rows, a.nrb, a.part);
         };
         if (a.cols % 4) launch(momentum_cols_partial<GT, true>, kThreads, 256);
-        else if (stream_waves(a.cols, a.nrb, a.batch) < kStreamWaves) launch(momentum_cols_partial<GT, false>, kThreads, 256);
+        else if (stream_waves(a.cols, a.nrb, a.batch) < kStreamWaves)
+            launch(momentum_cols_partial<GT, false>, kThreads, 256);
         else if (a.cols % (kThreads * 4) == 0) launch(momentum_cols_stream<GT>, kThreads, kThreads * 4);
         else launch(momentum_cols_stream<GT>, 64, 256);
         hipError_t e = hipGetLastError();
